@@ -206,14 +206,18 @@ void *scratch_ptr(int *status) {
 int status_of(hipError_t e) { return e == hipSuccess ? SHTX_OK : SHTX_ERR_HIP; }
 
 // Matrix-core Legendre kernels serve FP32 contraction from mfma_min_batch()
-// channels up: 5 for the analysis, 8 for the synthesis by default (below
-// that the 32-column matrix tiles are mostly padding and the vector-ALU
-// kernels are faster); SHTX_MFMA_MIN_BATCH sets both.  SHTX_FORCE_VALU=1 in
-// the environment selects the vector-ALU kernels everywhere.  Both are read
-// per call.
-int mfma_min_batch(bool synthesis) {
+// channels up (below that the 32-column matrix tiles are mostly padding and the
+// vector-ALU kernels are faster).  Analysis: 5.  Synthesis: 5, and 3 up to Nside
+// 256, where the vector-ALU kernels' launches per channel-group width and long
+// serial waves weigh more (matrix cores against vector ALUs: Nside 1024 L 2047
+// B 4 1.46 / 1.13 ms, B 5 1.48 / 1.72; Nside 512 L 1023 B 4 0.244 / 0.187,
+// B 5 0.234 / 0.301; Nside 256 L 511 B 2 0.047 / 0.045, B 3 0.048 / 0.091,
+// B 4 0.049 / 0.056; Nside 64 L 191 B 3 0.015 / 0.037).  SHTX_MFMA_MIN_BATCH
+// sets both.  SHTX_FORCE_VALU=1 in the environment selects the vector-ALU
+// kernels everywhere.  Both are read per call.
+int mfma_min_batch(bool synthesis, int nside) {
   const char *e = getenv("SHTX_MFMA_MIN_BATCH");
-  return e ? atoi(e) : synthesis ? 8 : 5;
+  return e ? atoi(e) : synthesis && nside <= 256 ? 3 : 5;
 }
 // FP64 transforms take the FP64 matrix cores from 3 channels for the
 // analysis and 5 for the synthesis (measured at Nside 1024: analysis 2.42 ms
@@ -243,7 +247,7 @@ template <> hipError_t legendre_fwd<double>(const Tables &tb, int B, const doubl
 }
 template <> hipError_t legendre_fwd<float>(const Tables &tb, int B, const float2 *XE, const float2 *XO, float2 *alm,
                                            double f0, double fm, int accum, hipStream_t st) {
-  if (B >= mfma_min_batch(false) && mfma_fwd_supported(tb) && !force_valu())
+  if (B >= mfma_min_batch(false, tb.nside) && mfma_fwd_supported(tb) && !force_valu())
     return launch_legendre_fwd_mfma(tb, B, XE, XO, alm, f0, fm, accum, st);
   return launch_legendre_fwd_valu<float>(tb, B, XE, XO, alm, f0, fm, accum, st);
 }
@@ -251,9 +255,9 @@ template <> hipError_t legendre_fwd<float>(const Tables &tb, int B, const float2
 // vector ALUs; the choice also fixes the channel groups of the coefficient
 // buffer (chan_group): one group of all channels for the matrix cores, the
 // vector-ALU kernels' groups otherwise.
-template <typename T> bool inv_on_mfma(int B) {
+template <typename T> bool inv_on_mfma(const Tables &tb, int B) {
   if (force_valu()) return false;
-  return sizeof(T) == 4 ? B >= mfma_min_batch(true) : B >= mfma64_min_batch(true);
+  return sizeof(T) == 4 ? B >= mfma_min_batch(true, tb.nside) : B >= mfma64_min_batch(true);
 }
 
 template <typename T> hipError_t legendre_inv(const Tables &tb, int B, const cplx<T> *ALMT, SynLayout lay,
@@ -281,7 +285,7 @@ template <typename TIn> bool bf16_contraction(const Tables &tb, int B) {
   } else {
     const char *e = getenv("SHTX_BF16_CONTRACT");
     if (e && e[0] == 'f') return false;
-    return B >= mfma_min_batch(false) && mfma_fwd_supported(tb) && !force_valu();
+    return B >= mfma_min_batch(false, tb.nside) && mfma_fwd_supported(tb) && !force_valu();
   }
 }
 
@@ -325,12 +329,13 @@ template <typename TOut, typename T>
 int run_synthesis(const Tables &tb, int B, const cplx<T> *alm, TOut *map, double s, double f0, double fm, void *work,
                   hipStream_t st, const TOut *sub = nullptr) {
   Work<T> w = carve<T>(work, tb, B);
-  const bool mfma = inv_on_mfma<T>(B);  // read once: both kernels follow the same choice
+  const bool mfma = inv_on_mfma<T>(tb, B);  // read once: both kernels follow the same choice
   hipError_t e;
   {
     StageTimer t(kStAlmIn, st);
     const int gmax = mfma ? B : sizeof(T) == 8 ? 2 : 4;
-    e = launch_alm_in<T, T>(tb.lmax, B, gmax, alm, tb.coefC, w.almt, s, f0, fm, st);
+    const double half = mfma && sizeof(T) == 4 ? 0.5 : 1.0;  // the FP32 matrix-core kernel doubles its sums
+    e = launch_alm_in<T, T>(tb.lmax, B, gmax, alm, tb.coefC, w.almt, half * s, f0, fm, st);
   }
   if (e != hipSuccess) return SHTX_ERR_HIP;
   {

@@ -352,6 +352,15 @@ template <> __device__ __forceinline__ void store_as<bf16_t, float>(bf16_t *p, f
   p->bits = (uint16_t)(u >> 16);
 }
 
+// FP64 -> FP32 kept as its own rounding step (left visible, the compiler
+// folds the two conversions FP64 -> FP32 -> BF16 into one direct FP64 -> BF16
+// rounding, a sequence of about ten instructions per value on this target).
+__device__ __forceinline__ float f64_to_f32(double d) {
+  float f = (float)d;
+  asm("" : "+v"(f));
+  return f;
+}
+
 // Two floats rounded to BF16 (nearest even) in one 32-bit word, `lo` in bits
 // 0-15: a complex value (re, im) of the BF16 ring spectra, or two Legendre
 // values of the BF16 matrix-core operands.

@@ -50,16 +50,6 @@ __device__ __forceinline__ f32x16_t mfma_bf16(u32x4_t a, u32x4_t b, f32x16_t c) 
                                                   0, 0, 0);
 }
 
-
-// FP64 -> FP32 kept as its own rounding step (left visible, the compiler
-// folds the two conversions FP64 -> FP32 -> BF16 into one direct FP64 -> BF16
-// rounding, a sequence of about ten instructions per value on this target).
-__device__ __forceinline__ float f64_to_f32(double d) {
-  float f = (float)d;
-  asm("" : "+v"(f));
-  return f;
-}
-
 constexpr int kBfWaves = 1;
 constexpr int kBfSlice = 128;                  // rings per wave slice
 constexpr int kBfChunk = kBfWaves * kBfSlice;  // rings per chunk

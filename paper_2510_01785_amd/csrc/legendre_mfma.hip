@@ -3,15 +3,20 @@
 // Eq. (24) are dense products
 //   analysis:  a[l, col]   = sum_p lambda_lm(z_p) X_{E/O}[p, col]   (K = ring pairs)
 //   synthesis: S[p, col]   = sum_l lambda_lm(z_p) a[l, col]         (K = l)
-// with col = (channel, re/im), 32 columns.  Both use v_mfma_f32_32x32x2_f32:
-// A is 32 x 2 (lane j holds A[j % 32][j / 32]), B is 2 x 32 (lane j holds
-// B[j / 32][j % 32]) and the 32 x 32 accumulator holds D[i][j] in lane
-// j + 32 ((i / 4) % 2), register 4 (i / 8) + i % 4.
+// with col = (channel, re/im), 32 columns.  The analysis uses
+// v_mfma_f32_32x32x2_f32: A is 32 x 2 (lane j holds A[j % 32][j / 32]), B is
+// 2 x 32 (lane j holds B[j / 32][j % 32]) and the 32 x 32 accumulator holds
+// D[i][j] in lane j + 32 ((i / 4) % 2), register 4 (i / 8) + i % 4.  The
+// synthesis takes its FP32 products as BF16 partial products (mfma_split2) with
+// v_mfma_f32_32x32x16_bf16: lane j holds A[j % 32][8 (j / 32) + e] and
+// B[8 (j / 32) + e][j % 32], e = 0..7; the accumulator is laid out the same.
 //
 // lambda is produced by the FP64 recurrence of Eq. (16) on mu = lambda / c
 // (tables.hip) with lanes running rings; in the synthesis that is already the
 // A layout (rows = rings, K = l), in the analysis the values go through a
 // wave-private LDS tile to become rows = l, K = rings.
+#include <type_traits>
+
 #include "common.h"
 
 namespace shtx {
@@ -255,34 +260,81 @@ __global__ void __launch_bounds__(64 * NW)
   }
 }
 
+// FP32 products on the BF16 matrix cores.  An FP32 value is the sum of three
+// BF16 values, x = h + m + l with each part the rounding of what the ones
+// before it leave (8 bits each, 24 in all; exact down to the subnormal range
+// of l), and a product of two such values is taken as the six partial products
+// hh + hm + mh + hl + lh + mm; the three left out are below 2^-26 of it.  All
+// of them are exact in FP32 and are added in FP32 by the matrix core, 16 terms
+// of K to a rounding (the FP32 instruction: 2), so the sums are no further
+// from the exact ones than FP32 products' (random operands, relative l2
+// against FP64: 6.8e-7 for FP32 products, K 2048: 8.4e-7).  Six
+// v_mfma_f32_32x32x16_bf16 take 192 cycles for what eight
+// v_mfma_f32_32x32x2_f32 take 512, and the vector ALU issues beside them
+// (beside FP32 matrix instructions it does not: both use its multipliers).
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x16 mfma_bf(u32x4 a, u32x4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                  0, 0);
+}
+// the three BF16 parts of two values, `x0` in bits 0-15 (the words are opaque
+// to the compiler, which would round the low halves a second time by themselves)
+__device__ __forceinline__ void split3(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l) {
+  h = pack_bf16x2(x0, x1);
+  asm("" : "+v"(h));
+  const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
+  m = pack_bf16x2(r0, r1);
+  asm("" : "+v"(m));
+  l = pack_bf16x2(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
+}
+// c0 += a0 b, c1 += a1 b for operands in three parts, small products first and
+// alternating (no product waits for the one before it)
+__device__ __forceinline__ void mfma_split2(const u32x4 (&a0)[3], const u32x4 (&a1)[3], const u32x4 (&b)[3],
+                                            f32x16 &c0, f32x16 &c1) {
+  constexpr int ia[6] = {0, 2, 1, 0, 1, 0}, ib[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    c0 = mfma_bf(a0[ia[k]], b[ib[k]], c0);
+    c1 = mfma_bf(a1[ia[k]], b[ib[k]], c1);
+  }
+}
+
 // Synthesis.  Workgroup = one wave = (m, chunk of 64 ring pairs), one ring
-// per lane.  Per 8 steps of l every lane advances its ring's recurrence by 8
-// values; v_permlane32_swap pairs them into the A operands of the 32-ring
-// halves (lanes 0-31: lambda_l, lanes 32-63: lambda_{l+2} of the same 32
-// rings), so that with B = a_{l}, a_{l+2} (even MFMA) and a_{l+1}, a_{l+3}
-// (odd MFMA) of 16 channels each half takes 4 MFMAs per 8 steps and no ring's
-// recurrence is computed twice.  The recurrence coefficients are wave-uniform
-// scalar loads and the B operands come straight from the coefficient slab
-// (L1/L2), one group ahead: no LDS, no barriers, and every wave starts at its
-// own rings' first non-negligible l.  Workgroups are dealt so that all chunks
+// per lane, NC groups of 16 channels.  Per 32 steps of l every lane advances
+// its ring's recurrence by 32 values, splits them and packs the 16 even and
+// the 16 odd ones into the words of the A operands: v_permlane32_swap gives
+// the 32-ring halves (lanes 0-31 the first 8 values of one parity, lanes
+// 32-63 the last 8 of the same 32 rings), so no ring's recurrence is computed
+// twice.  The B operands a[l][col] come as FP32 rows of the coefficient slab
+// (L1/L2), loaded before the recurrence that hides their latency and split
+// after it.  The recurrence coefficients are wave-uniform scalar loads, one
+// group of 8 ahead.  No LDS, no barriers, and every wave starts at its own
+// rings' first non-negligible l.  Workgroups are dealt so that all chunks
 // of eight consecutive m run on one XCD (consecutive workgroups go to
 // consecutive XCDs): they share the a_m slabs in L2.  A wave writes, per ring
 // pair, whole [m][batch] rows of the synthesis spectra (32 consecutive floats
-// per ring: one 128-byte line at 16 channels).
+// per ring: one 128-byte line at 16 channels).  The slab holds half of each
+// coefficient (so that no finite one rounds up to a BF16 infinity); the sums
+// are doubled as they are stored.
+//
+// Bound by the vector ALU: per group of 32 l some 400 vector instructions
+// (recurrence 72, conversions 32, splitting of lambda 176 and of the rows 88,
+// half exchanges 24) beside 24 matrix instructions.  Timing copies (Nside 1024
+// L 2047 B 16, 1.72 ms): without the matrix instructions 1.31 ms, without
+// splitting lambda 1.35, without splitting the rows 1.52, without the half
+// exchanges 1.65.  FP32 matrix instructions in this place took 2.03 ms (Nside
+// 512 L 1535 B 12 0.67 -> 0.52 ms; Nside 256 L 767 B 64, two channel groups per
+// wave, 0.40 -> 0.30 ms).  One group of channels runs three waves per SIMD
+// (160 VGPRs; 1.88 ms with two), two groups two (242 VGPRs).
 constexpr int kInvRings = 64;
 
-// (lanes 0-31 of x | lanes 0-31 of y) and (lanes 32-63 of x | lanes 32-63 of y)
-__device__ __forceinline__ void pair_halves(float x, float y, float &lo, float &hi) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-  lo = __uint_as_float(r[0]);
-  hi = __uint_as_float(r[1]);
-}
-
-__global__ void __launch_bounds__(64)
-    k_legendre_inv_mfma(Tables tb, int B, const double *__restrict__ coefA, const float2 *__restrict__ ALMT,
+template <int NC>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NC == 1 ? 3 : 2, NC == 1 ? 3 : 2)))
+    k_legendre_inv_mfma(Tables tb, int B, int bg, const double *__restrict__ coefA, const float2 *__restrict__ ALMT,
                         SynLayout lay, float2 *__restrict__ GN, float2 *__restrict__ GS) {
-  const int b0 = 16 * blockIdx.y;  // channel group of this row of the grid
-  const int L = tb.lmax, M = L + 1, Rp = tb.npairs;
+  const int b0 = bg + 16 * NC * blockIdx.y;  // first channel of this row of the grid
+  const int L = tb.lmax, Rp = tb.npairs;
   const int nch = (Rp + kInvRings - 1) / kInvRings;
   const int g = blockIdx.x;
   const int x = g & 7, q = g >> 3;
@@ -296,147 +348,154 @@ __global__ void __launch_bounds__(64)
   const int h = j >> 5, col = j & 31;
   const int p = chunk * kInvRings + j;
   const bool pok = p < Rp;
-  const bool colok = (b0 + (col >> 1)) < B;
   const double z = pok ? tb.rp_z[p] : 0.0;
   const int ls = pok ? tb.seed_l[(size_t)m * Rp + p] : L + 1;
   const double2 sd = pok ? tb.seed_v[(size_t)m * Rp + p] : make_double2(0.0, 0.0);
-  // first l any ring of each 32-ring half needs (aligned to m + 8j like every
-  // seed), and the last seed of the wave (after it no ring starts: steps
-  // without the injection selects)
-  int wh = ls, wx = pok && ls <= L ? ls : -1;
+  // first l any ring of the chunk needs (m + 8j, like every seed)
+  int wh = ls;
 #pragma unroll
-  for (int o = 1; o < 32; o <<= 1) wh = min(wh, __shfl_xor(wh, o));
+  for (int o = 1; o < 64; o <<= 1) wh = min(wh, __shfl_xor(wh, o));
+  const int wl = __builtin_amdgcn_readfirstlane(wh);
+  f32x16 acc[NC][4];
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) wx = max(wx, __shfl_xor(wx, o));
-  const int wl0 = __builtin_amdgcn_readfirstlane(wh);
-  const int wl1 = __builtin_amdgcn_readfirstlane(__shfl(wh, 32));
-  const int wl = min(wl0, wl1);
-  const int wlast = __builtin_amdgcn_readfirstlane(wx);
-  f32x16 acc[4];
+  for (int n = 0; n < NC; ++n)
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[a][r] = 0.f;
+      for (int r = 0; r < 16; ++r) acc[n][a][r] = 0.f;
   // A[l] of this m through the constant address space: wave-uniform indices
   // become scalar loads into SGPRs
   // (32-bit index arithmetic keeps the address on the scalar unit; nalm < 2^31)
   typedef __attribute__((address_space(4))) const double cdouble;
   const int aoff = m * (2 * L + 1 - m) / 2;  // alm_idx(m, m, L) - m
   const cdouble *Ag = (const cdouble *)coefA + aoff;
-  // this lane's column of the coefficient slab a[l][col] (channels beyond the
-  // batch read channel B-1: finite data, outputs not stored)
-  const int colc = colok ? col : 2 * (B - 1 - b0) + (col & 1);
-  // slab of column m (uniform) and this lane's fixed offsets in it: B operands
-  // of the group starting at lq are rows lq + 2h + {0, 1, 4, 5}.  Rows past
-  // lmax (at most 7, inside the padded coefficient workspace) are read and
-  // then zeroed with their lambda in the last group.
-  // Buffer loads: the slab's base in the resource, the lane's offsets in
-  // VGPRs and the group's row offset in an SGPR (no per-load vector address
-  // arithmetic); the slab of one m is below 2^32 bytes for any supported
-  // (lmax, batch) that fits the device.
-  const float *ag = reinterpret_cast<const float *>(ALMT) + ((size_t)aoff * B + b0) * 2;
-  const unsigned arow = 2u * (unsigned)B;
-  const unsigned vo0 = (2u * h * arow + colc) * 4u, vo1 = vo0 + arow * 4u, vo4 = vo0 + 16u * arow,
-                 vo5 = vo0 + 20u * arow;
-  const __amdgpu_buffer_rsrc_t ar = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(ag), 0, 0xffffffff,
-                                                                       kBufferWord3);
-  auto fetchB = [&](int lq, float (&bv)[4]) {
-    const unsigned so = (unsigned)lq * arow * 4u;
-    bv[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ar, vo0, so, 0));
-    bv[1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ar, vo1, so, 0));
-    bv[2] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ar, vo4, so, 0));
-    bv[3] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ar, vo5, so, 0));
-  };
+  // B operands of the group from lq: lane (h, col) takes rows lq + 16 h + 2 e
+  // + parity, e = 0..7.  The slab of column m is a buffer resource that ends
+  // after row lmax: rows past it read as zero and need no mask (the bounds check
+  // covers the VGPR offset, the lane's, plus the SGPR offset, the row's, which
+  // stays within the resource).
+  // Channels past the batch read channel B-1 (finite data, not stored).
+  const float *ag = reinterpret_cast<const float *>(ALMT) + (size_t)aoff * B * 2;
+  const unsigned rowb = 8u * (unsigned)B;  // bytes per row; (lmax + 1) rows of one m are below 2^32 bytes
+  const __amdgpu_buffer_rsrc_t ar = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float *>(ag), 0, (int)((unsigned)(L + 1) * rowb), kBufferWord3);
+  unsigned vo[NC];
+#pragma unroll
+  for (int n = 0; n < NC; ++n) {
+    const int c = min(b0 + 16 * n + (col >> 1), B - 1);
+    vo[n] = 16u * h * rowb + 8u * c + 4u * (col & 1);
+  }
   double prv = 0.0, cur = 0.0;
-  // one group of 8 steps from l = lq with its operands bc (B) and ac (A_l);
-  // the next group's operands go to bn, an (the last group re-reads its own
-  // rows: every group issues the same loads, so the waits count exactly).
-  // Two register sets alternate: no copies, and a group waits only for the
-  // loads issued one group earlier (scalar loads complete out of order, so a
-  // wait for one is a wait for all: the next ones go after this group's).
-  auto group = [&](int lq, const float (&bc)[4], const double (&ac)[8], float (&bn)[4], double (&an)[8]) {
-    const int ln = lq + 8 <= L ? lq + 8 : lq;
-    fetchB(ln, bn);
-    // the next group's scalar loads take an address that is known only
-    // once this group's A_l have arrived, so they are issued after that wait
-    // (and a group ahead of their own)
-    int la = ln;
-    asm volatile("" : "+s"(la) : "s"(ac[7]));
+  // One group of 32 steps from l = lq; ac holds A_l of its first 8 steps and
+  // receives those of the next group's.  TAIL: the group holds l > lmax, whose
+  // coefficients are taken as zero (the recurrence stays finite there and
+  // meets zero rows of B).
+  auto group = [&](int lq, double (&ac)[8], auto tail) {
+    constexpr bool TAIL = decltype(tail)::value;
+    float bf[NC][2][8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) an[u] = Ag[la + u];
-    float lam[8];
-    // a ring's state is exactly zero before its seed, so the seed enters as a
-    // 0/1 factor on two fused multiply-adds (no selects, no branch)
-    const double f = (lq == ls) ? 1.0 : 0.0;
+    for (int e = 0; e < 8; ++e)
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const double nx = fma(ac[u] * z, cur, -prv);
-      if (u == 0) {
-        prv = fma(f, sd.x, cur);
-        cur = fma(f, sd.y, nx);
-      } else {
-        prv = cur;
-        cur = nx;
+      for (int par = 0; par < 2; ++par) {
+        const int row = lq + 2 * e + par;
+        const unsigned so = (unsigned)(TAIL ? min(row, L + 1) : row) * rowb;
+#pragma unroll
+        for (int n = 0; n < NC; ++n)
+          bf[n][par][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ar, vo[n], so, 0));
       }
-      lam[u] = (float)cur;
-    }
-    float bb[4] = {bc[0], bc[1], bc[2], bc[3]};
-    if (lq + 7 > L) {  // last group: l beyond lmax contributes nothing
+    asm volatile("" ::: "memory");  // issued here, ahead of the recurrence
+    uint32_t w[2][3][8];            // [parity][part][pair of l]
 #pragma unroll
-      for (int u = 0; u < 8; ++u) lam[u] = (lq + u <= L) ? lam[u] : 0.f;
-      const int r0 = lq + 2 * h;
-      bb[0] = r0 <= L ? bb[0] : 0.f;
-      bb[1] = r0 + 1 <= L ? bb[1] : 0.f;
-      bb[2] = r0 + 4 <= L ? bb[2] : 0.f;
-      bb[3] = r0 + 5 <= L ? bb[3] : 0.f;
+    for (int s = 0; s < 4; ++s) {
+      const int l8 = lq + 8 * s;
+      double an[8];
+      int la = l8 + 8;
+      if (la > L) la = l8;
+      asm volatile("" : "+s"(la) : "s"(ac[7]));
+#pragma unroll
+      for (int u = 0; u < 8; ++u) an[u] = Ag[la + u];
+      __builtin_amdgcn_sched_barrier(0);  // issued here, a group of 8 ahead of their use
+      // a ring's state is exactly zero before its seed, so the seed enters as a
+      // 0/1 factor on two fused multiply-adds (no selects, no branch)
+      const double f = (l8 == ls) ? 1.0 : 0.0;
+      float lam[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const double a = !TAIL || l8 + u <= L ? ac[u] : 0.0;
+        const double nx = fma(a * z, cur, -prv);
+        if (u == 0) {
+          prv = fma(f, sd.x, cur);
+          cur = fma(f, sd.y, nx);
+        } else {
+          prv = cur;
+          cur = nx;
+        }
+        lam[u] = f64_to_f32(cur);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int par = 0; par < 2; ++par)
+          split3(lam[4 * i + par], lam[4 * i + 2 + par], w[par][0][2 * s + i], w[par][1][2 * s + i],
+                 w[par][2][2 * s + i]);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) ac[u] = an[u];
     }
-    float e0lo, e0hi, o0lo, o0hi, e1lo, e1hi, o1lo, o1hi;
-    pair_halves(lam[0], lam[2], e0lo, e0hi);
-    pair_halves(lam[1], lam[3], o0lo, o0hi);
-    pair_halves(lam[4], lam[6], e1lo, e1hi);
-    pair_halves(lam[5], lam[7], o1lo, o1hi);
-    if (lq + 7 >= wl0) {
-      acc[0] = mfma32(e0lo, bb[0], acc[0]);
-      acc[1] = mfma32(o0lo, bb[1], acc[1]);
-      acc[0] = mfma32(e1lo, bb[2], acc[0]);
-      acc[1] = mfma32(o1lo, bb[3], acc[1]);
-    }
-    if (lq + 7 >= wl1) {
-      acc[2] = mfma32(e0hi, bb[0], acc[2]);
-      acc[3] = mfma32(o0hi, bb[1], acc[3]);
-      acc[2] = mfma32(e1hi, bb[2], acc[2]);
-      acc[3] = mfma32(o1hi, bb[3], acc[3]);
+#pragma unroll
+    for (int par = 0; par < 2; ++par) {
+      __builtin_amdgcn_sched_barrier(0);
+      u32x4 a0[3], a1[3];  // rings 0-31 and 32-63 of the chunk
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const auto r = __builtin_amdgcn_permlane32_swap(w[par][k][i], w[par][k][i + 4], false, false);
+          a0[k][i] = r[0];
+          a1[k][i] = r[1];
+        }
+#pragma unroll
+      for (int n = 0; n < NC; ++n) {
+        u32x4 b[3];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          uint32_t bh, bm, bl;
+          split3(bf[n][par][2 * i], bf[n][par][2 * i + 1], bh, bm, bl);
+          b[0][i] = bh;
+          b[1][i] = bm;
+          b[2][i] = bl;
+        }
+        mfma_split2(a0, a1, b, acc[n][par], acc[n][2 + par]);
+      }
     }
   };
-  float bA[4], bB[4];
-  double aA[8], aB[8];  // A_l of the groups (scalar registers)
   if (wl <= L) {
-    fetchB(wl, bA);
+    double ac[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) aA[u] = Ag[wl + u];
-  }
+    for (int u = 0; u < 8; ++u) ac[u] = Ag[wl + u];
+    int lq = wl;
 #pragma unroll 1
-  for (int lq = wl; lq <= L; lq += 16) {
-    group(lq, bA, aA, bB, aB);
-    if (lq + 8 > L) break;
-    group(lq + 8, bB, aB, bA, aA);
+    for (; lq + 31 <= L; lq += 32) group(lq, ac, std::false_type{});
+    if (lq <= L) group(lq, ac, std::true_type{});
   }
-  if (!colok) return;
   float *gn = reinterpret_cast<float *>(GN);
   float *gs = reinterpret_cast<float *>(GS);
-  const int c = b0 + (col >> 1);
   const size_t ringf = (size_t)lay.ns * lay.M * lay.G * 2;  // floats per ring pair
-  const size_t cofs = lay.idx(0, c, m) * 2 + (col & 1);
 #pragma unroll
-  for (int hh = 0; hh < 2; ++hh) {
+  for (int n = 0; n < NC; ++n) {
+    const int c = b0 + 16 * n + (col >> 1);
+    if (c >= B) continue;
+    const size_t cofs = lay.idx(0, c, m) * 2 + (col & 1);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int i = 8 * (r >> 2) + 4 * h + (r & 3);
-      const int pr = chunk * kInvRings + hh * 32 + i;
-      if (pr >= Rp) continue;
-      const size_t o = (size_t)pr * ringf + cofs;
-      gn[o] = acc[2 * hh][r] + acc[2 * hh + 1][r];
-      gs[o] = acc[2 * hh][r] - acc[2 * hh + 1][r];
+    for (int hh = 0; hh < 2; ++hh) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int i = 8 * (r >> 2) + 4 * h + (r & 3);
+        const int pr = chunk * kInvRings + hh * 32 + i;
+        if (pr >= Rp) continue;
+        const size_t o = (size_t)pr * ringf + cofs;
+        gn[o] = 2.f * (acc[n][2 * hh][r] + acc[n][2 * hh + 1][r]);
+        gs[o] = 2.f * (acc[n][2 * hh][r] - acc[n][2 * hh + 1][r]);
+      }
     }
   }
 }
@@ -475,8 +534,14 @@ hipError_t launch_legendre_inv_mfma(const Tables &tb, int B, const float2 *ALMT,
   const int nch = (tb.npairs + kInvRings - 1) / kInvRings;
   const int noct = (tb.lmax + 1 + 7) / 8;
   const int per_xcd = ((noct + 7) / 8) * 8 * nch;  // octets per XCD x 8 m x chunks
-  hipLaunchKernelGGL(k_legendre_inv_mfma, dim3(8 * per_xcd, (B + 15) / 16), dim3(64), 0, st, tb, B, tb.coefA,
-                     ALMT, lay, GN, GS);
+  // pairs of 16-channel groups share a wave's recurrence; then one group
+  const int n32 = (B + 15) / 32;
+  if (n32 > 0)
+    hipLaunchKernelGGL(k_legendre_inv_mfma<2>, dim3(8 * per_xcd, n32), dim3(64), 0, st, tb, B, 0, tb.coefA, ALMT, lay,
+                       GN, GS);
+  if (32 * n32 < B)
+    hipLaunchKernelGGL(k_legendre_inv_mfma<1>, dim3(8 * per_xcd, 1), dim3(64), 0, st, tb, B, 32 * n32, tb.coefA, ALMT,
+                       lay, GN, GS);
   return hipGetLastError();
 }
 

@@ -1,0 +1,76 @@
+"""Legendre kernels whose FP32 products run as BF16 partial products on the
+matrix cores, at the edges of their tiles: against the FP64 oracle at the FP32
+tolerance of the transforms (1e-5 relative l2; the products carry 24 bits)."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import sht
+from paper_2510_01785_amd import synth
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5
+
+
+@pytest.fixture(scope="module")
+def shtx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2510_01785_amd as m
+    return m
+
+
+def rel_l2(got, ref):
+    return float(np.linalg.norm((got - ref).ravel()) / np.linalg.norm(ref.ravel()))
+
+
+# one and two groups of 16 channels per wave, partial groups; columns of m that
+# end inside, at and just past a group of 32 l (every m = 0..L is one); fewer,
+# as many and more ring pairs than a chunk of 64; band limits below 8
+@pytest.mark.parametrize("nside,lmax,batch", [(1, 0, 3), (2, 7, 5), (8, 31, 16), (8, 32, 17), (16, 47, 31),
+                                              (32, 63, 32), (32, 64, 33), (64, 101, 48), (64, 191, 3), (128, 130, 7)])
+def test_synthesis_edges(shtx, nside, lmax, batch):
+    print("\n[case] synthesis nside=%d lmax=%d B=%d" % (nside, lmax, batch), flush=True)
+    alm = synth.random_alm(nside + lmax + batch, batch, lmax).astype(np.complex64)
+    got = shtx.alm2map_raw(torch.tensor(alm, device="cuda"), nside, lmax).cpu().numpy()
+    assert rel_l2(got, sht.alm2map(alm.astype(np.complex128), nside, lmax)) <= TOL
+
+
+def test_synthesis_reads_nothing_past_the_coefficients(shtx):
+    """A workspace full of NaN changes nothing (rows past lmax and channels
+    past the batch meet no product), and a NaN channel stays in its channel."""
+    from paper_2510_01785_amd import _lib
+    nside, lmax, B = 16, 42, 9
+    print("\n[case] synthesis, NaN workspace", flush=True)
+    alm = torch.tensor(synth.random_alm(5, B, lmax).astype(np.complex64), device="cuda")
+    want = shtx.alm2map_raw(alm, nside, lmax)
+    L = _lib.lib()
+    nb = L.shtx_workspace_bytes(nside, lmax, B, _lib.F32)
+    work = torch.full((nb // 4,), float("nan"), device="cuda")
+    out = torch.empty_like(want)
+    st = L.shtx_alm2map(nside, lmax, B, _lib.F32, alm.data_ptr(), out.data_ptr(),
+                        shtx.get_tables(nside, lmax, alm.device).data_ptr(), work.data_ptr(), ctypes.c_size_t(nb),
+                        torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    assert torch.equal(out, want)
+    alm[4] = float("nan")
+    got = shtx.alm2map_raw(alm, nside, lmax)
+    keep = [b for b in range(B) if b != 4]
+    assert torch.equal(got[keep], want[keep]) and torch.isnan(got[4]).all()
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e30, float(np.finfo(np.float32).max)])
+def test_synthesis_coefficient_range(shtx, scale):
+    """Small and large coefficients, up to the largest finite one (a_00 alone:
+    a constant map below the FP32 limit)."""
+    print("\n[case] synthesis, coefficients of %g" % scale, flush=True)
+    nside, lmax, B = 16, 40, 5
+    alm = np.zeros((B, synth.nalm(lmax)), dtype=np.complex64)
+    alm[:, 0] = scale
+    if scale < 1e31:
+        alm = (synth.random_alm(6, B, lmax) * scale).astype(np.complex64)
+    got = shtx.alm2map_raw(torch.tensor(alm, device="cuda"), nside, lmax).cpu().numpy().astype(np.float64)
+    ref = sht.alm2map(alm.astype(np.complex128), nside, lmax)
+    assert np.isfinite(got).all() and rel_l2(got / scale, ref / scale) <= TOL
