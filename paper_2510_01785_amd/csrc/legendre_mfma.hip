@@ -3,13 +3,11 @@
 // Eq. (24) are dense products
 //   analysis:  a[l, col]   = sum_p lambda_lm(z_p) X_{E/O}[p, col]   (K = ring pairs)
 //   synthesis: S[p, col]   = sum_l lambda_lm(z_p) a[l, col]         (K = l)
-// with col = (channel, re/im), 32 columns.  The analysis uses
-// v_mfma_f32_32x32x2_f32: A is 32 x 2 (lane j holds A[j % 32][j / 32]), B is
-// 2 x 32 (lane j holds B[j / 32][j % 32]) and the 32 x 32 accumulator holds
-// D[i][j] in lane j + 32 ((i / 4) % 2), register 4 (i / 8) + i % 4.  The
-// synthesis takes its FP32 products as BF16 partial products (mfma_split2) with
-// v_mfma_f32_32x32x16_bf16: lane j holds A[j % 32][8 (j / 32) + e] and
-// B[8 (j / 32) + e][j % 32], e = 0..7; the accumulator is laid out the same.
+// with col = (channel, re/im), 32 columns.  Both take their FP32 products as BF16
+// partial products (below) with v_mfma_f32_32x32x16_bf16: lane j holds
+// A[j % 32][8 (j / 32) + e] and B[8 (j / 32) + e][j % 32], e = 0..7, and the
+// 32 x 32 accumulator holds D[i][j] in lane j + 32 ((i / 4) % 2), register
+// 4 (i / 8) + i % 4.
 //
 // lambda is produced by the FP64 recurrence of Eq. (16) on mu = lambda / c
 // (tables.hip) with lanes running rings; in the synthesis that is already the
@@ -22,8 +20,75 @@
 namespace shtx {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-__device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+// FP32 products on the BF16 matrix cores.  An FP32 value is the sum of three
+// BF16 values, x = h + m + l with each part the rounding of what the ones
+// before it leave (8 bits each, 24 in all; exact down to the subnormal range
+// of l), and a product of two such values is taken as the six partial products
+// hh + hm + mh + hl + lh + mm; the three left out are below 2^-26 of it.  All
+// of them are exact in FP32 and are added in FP32 by the matrix core, 16 terms
+// of K to a rounding (the FP32 instruction: 2), so the sums are no further
+// from the exact ones than FP32 products' (random operands, relative l2
+// against FP64: 6.8e-7 for FP32 products, K 2048: 8.4e-7).  Six
+// v_mfma_f32_32x32x16_bf16 take 192 cycles for what eight
+// v_mfma_f32_32x32x2_f32 take 512, and the vector ALU issues beside them
+// (beside FP32 matrix instructions it does not: both use its multipliers).
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x16 mfma_bf(u32x4 a, u32x4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                  0, 0);
+}
+// The three BF16 parts of two values in words i of p[0..2], x0 in bits 0-15 (the
+// words are opaque to the compiler, which would round the low halves a second
+// time by themselves).  What a part leaves, x - part, is exact; DOT forms it as
+// a two-term dot product with (-1, 0) or (0, -1) instead of a shift or mask and
+// a subtraction: fewer instructions, each longer.  Analysis 2.22 -> 2.18 ms
+// with it, synthesis 1.69 -> 1.78 (Nside 1024 L 2047 B 16).
+__device__ __forceinline__ float dot_bf(uint32_t a, uint32_t b, float c) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, b), c, false);
+}
+template <bool DOT, typename V> __device__ __forceinline__ void split3(float x0, float x1, V (&p)[3], int i) {
+  uint32_t h = pack_bf16x2(x0, x1), m;
+  asm("" : "+v"(h));
+  float r0, r1;
+  if constexpr (DOT) {
+    uint32_t n0 = 0x0000bf80u, n1 = 0xbf800000u;
+    asm("" : "+s"(n0), "+s"(n1));  // in registers: a literal operand would be repeated in both halves
+    r0 = dot_bf(h, n0, x0);
+    r1 = dot_bf(h, n1, x1);
+    m = pack_bf16x2(r0, r1);
+    asm("" : "+v"(m));
+    r0 = dot_bf(m, n0, r0);
+    r1 = dot_bf(m, n1, r1);
+  } else {
+    r0 = x0 - __uint_as_float(h << 16);
+    r1 = x1 - __uint_as_float(h & 0xffff0000u);
+    m = pack_bf16x2(r0, r1);
+    asm("" : "+v"(m));
+    r0 -= __uint_as_float(m << 16);
+    r1 -= __uint_as_float(m & 0xffff0000u);
+  }
+  p[0][i] = h;
+  p[1][i] = m;
+  p[2][i] = pack_bf16x2(r0, r1);
+}
+// c += a b for operands in three parts, small products first
+__device__ __forceinline__ void mfma_split(const u32x4 (&a)[3], const u32x4 (&b)[3], f32x16 &c) {
+  constexpr int ia[6] = {0, 2, 1, 0, 1, 0}, ib[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+  for (int k = 0; k < 6; ++k) c = mfma_bf(a[ia[k]], b[ib[k]], c);
+}
+// the same for two left operands, alternating (no product waits for the one
+// before it)
+__device__ __forceinline__ void mfma_split2(const u32x4 (&a0)[3], const u32x4 (&a1)[3], const u32x4 (&b)[3],
+                                            f32x16 &c0, f32x16 &c1) {
+  constexpr int ia[6] = {0, 2, 1, 0, 1, 0}, ib[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    c0 = mfma_bf(a0[ia[k]], b[ib[k]], c0);
+    c1 = mfma_bf(a1[ia[k]], b[ib[k]], c1);
+  }
 }
 
 // Word 3 of a raw buffer resource on gfx9-family GPUs (untyped 32-bit
@@ -38,18 +103,25 @@ static_assert(kBlockL * kRedRS <= kSubL * kTileRS, "reduction fits the tile");
 // NW waves take 64-ring slices of every 64 NW-ring chunk; each lane restarts its
 // ring's recurrence from the block checkpoint, writes 64 lambdas per sub-tile
 // into its wave's LDS tile [l][ring], and the wave multiplies the tile (rows =
-// even or odd l) with the ring spectra E or O held in registers.  The NW
-// waves' partial sums are added through LDS at the end.  NW = 1 or 2 (launch
-// choice): smaller workgroups than four waves measured faster at every size
-// (more of them, a shorter cross-wave reduction and barriers over fewer
-// waves).
+// even or odd l) with the ring spectra E or O, split once per slice and held in
+// registers.  The NW waves' partial sums are added through LDS at the end.
+// NW = 1 or 2 (launch choice): smaller workgroups than four waves measured
+// faster at every size (more of them, a shorter cross-wave reduction and
+// barriers over fewer waves).
+//
+// Bound by the vector ALU at two waves per SIMD (256 VGPRs: 64 of sums, 96 of
+// split spectra), and by power: the card runs it at about 2.0 GHz, FP32 matrix
+// instructions in its place at 2.3.  Timing copies (Nside 1024 L 2047 B 16, 2.2
+// ms): without the recurrence 1.6 ms, without the matrix instructions 1.75,
+// without splitting lambda 1.9, without splitting the spectra 2.0.  FP32 matrix
+// instructions took 2.35 ms (Nside 512 L 1535 B 12 0.80 -> 0.72 ms, Nside 256
+// L 767 B 64 0.52 -> 0.46, Nside 128 L 301 B 5 0.028 -> 0.025).
 template <int NW>
-__global__ void __launch_bounds__(64 * NW)
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     k_legendre_fwd_mfma(Tables tb, int B, const double *__restrict__ coefA, const float2 *__restrict__ XE,
                         const float2 *__restrict__ XO, float2 *__restrict__ alm, float f0, float fm, int accum) {
   const int b0 = 16 * blockIdx.y;  // channel group of this row of the grid
   __shared__ float tile[NW * kSubL * kTileRS];
-  __shared__ double sA[kBlockL];
   const int g = blockIdx.x;
   const int x = g & 7, k = g >> 3;
   const int i0 = tb.ck_xoff[x];
@@ -65,11 +137,11 @@ __global__ void __launch_bounds__(64 * NW)
   // floats per ring pair in X; the fast load path needs 32 of them in 32 bits
   const size_t rowf = (size_t)M * B * 2;
   const bool fast_rows = rowf * 32 * sizeof(float) < (size_t)0x7fffffff;
-  {
-    const double *Ag = coefA + alm_idx(m, m, L) - m;
-    for (int t = tid; t < kBlockL; t += 64 * NW) sA[t] = Ag[min(l0 + t, L)];
-  }
-  __syncthreads();
+  // the block's recurrence coefficients through the constant address space:
+  // wave-uniform scalar loads (rows past lmax, never stored, read other columns
+  // or the table's padding)
+  typedef __attribute__((address_space(4))) const double cdouble;
+  const cdouble *Ag = (const cdouble *)coefA + (m * (2 * L + 1 - m) / 2 + l0);  // nalm < 2^31
   float *tw = tile + w * kSubL * kTileRS;
   const float *xe_f = reinterpret_cast<const float *>(XE);
   const float *xo_f = reinterpret_cast<const float *>(XO);
@@ -111,15 +183,15 @@ __global__ void __launch_bounds__(64 * NW)
     }
     const int tlast = __builtin_amdgcn_readfirstlane(tx);
     const int tfirst = __builtin_amdgcn_readfirstlane(tn);
-    // B operands: K-step s pairs ring c0+64w+s (lanes < 32) with ring +32 (lanes >= 32)
-    float xe[32], xo[32];
+    // B operands: K step s, element e of lane half h is ring c0 + 64 w + 16 s +
+    // 8 h + e; FP32 values here, split after the recurrence that covers the loads
+    float xf[2][32];             // [E, O][8 s + e]
     const int rw = c0 + w * 64;  // first ring of this wave's slice (uniform)
     if (fast_rows && rw + 64 <= Rp) {
-      // uniform row address per step, one 32-bit lane offset (half, column)
       // buffer loads: one resource per slice (uniform base), the lane's byte
-      // offset in a VGPR and the step's row offset in an SGPR, so no per-load
-      // vector address arithmetic (offsets < 2^32 by fast_rows)
-      const unsigned voff = (unsigned)(h * 32 * rowf + colc) * 4u;
+      // offset (half, column) in a VGPR and the ring's row offset in an SGPR, so
+      // no per-load vector address arithmetic (offsets < 2^32 by fast_rows)
+      const unsigned voff = (unsigned)(h * 8 * rowf + colc) * 4u;
       const size_t o0 = ((size_t)rw * M + m) * B * 2 + (size_t)b0 * 2;
       const __amdgpu_buffer_rsrc_t re = __builtin_amdgcn_make_buffer_rsrc(
           const_cast<float *>(xe_f + o0), 0, 0xffffffff, kBufferWord3);
@@ -127,47 +199,42 @@ __global__ void __launch_bounds__(64 * NW)
           const_cast<float *>(xo_f + o0), 0, 0xffffffff, kBufferWord3);
 #pragma unroll
       for (int s = 0; s < 32; ++s) {
-        const unsigned so = (unsigned)(s * rowf) * 4u;
-        xe[s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(re, voff, so, 0));
-        xo[s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ro, voff, so, 0));
+        const unsigned so = (unsigned)((16 * (s >> 3) + (s & 7)) * rowf) * 4u;
+        xf[0][s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(re, voff, so, 0));
+        xf[1][s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ro, voff, so, 0));
       }
     } else {
       // rings beyond the last pair read the last pair (their lambda is zero)
 #pragma unroll
       for (int s = 0; s < 32; ++s) {
-        const int r = min(rw + h * 32 + s, Rp - 1);
+        const int r = min(rw + 16 * (s >> 3) + 8 * h + (s & 7), Rp - 1);
         const size_t o = (((size_t)r * M + m) * B + b0) * 2 + colc;
-        xe[s] = xe_f[o];
-        xo[s] = xo_f[o];
+        xf[0][s] = xe_f[o];
+        xf[1][s] = xo_f[o];
       }
     }
     // issue the loads here, ahead of the recurrence (left alone, the compiler
     // sinks them to their first use after it and their latency is exposed)
     asm volatile("" ::: "memory");
     double prv = 0.0, cur = 0.0;
+    // 64 steps of the recurrence from l0 + base, one lambda per lane per step
+    // into the tile (rows: the half block's 32 even l, then its 32 odd l)
+    auto recurrence = [&](int base) {
+      double Ac[8];
 #pragma unroll
-    for (int hb = 0; hb < 2; ++hb) {
-      // half blocks with no lambda: every ring of the wave starts after it
-      // (the recurrence state stays zero until its start), or every l of it
-      // is beyond lmax (output rows that are never stored)
-      if (hb == 0 && tfirst >= kSubL) continue;
-      if (hb == 1 && l0 + kSubL > L) continue;
-      // recurrence: 64 steps, one lambda per lane per step into the tile
+      for (int u = 0; u < 8; ++u) Ac[u] = Ag[base + u];
 #pragma unroll 1
       for (int t8 = 0; t8 < kSubL / 8; ++t8) {
-        const int tb8 = hb * kSubL + t8 * 8;
-        // the group's coefficients: one lane-uniform LDS address, four
-        // 16-byte reads at immediate offsets
-        int aaddr = tb8;
-        asm volatile("" : "+v"(aaddr));
-        const double2 *sA2 = reinterpret_cast<const double2 *>(sA + aaddr);
-        double Ac[8];
+        const int tb8 = base + t8 * 8;
+        // the next group's coefficients, once this group's have arrived (scalar
+        // loads complete out of order: a wait for one is a wait for all)
+        double An[8];
+        int ta = tb8 + 8;
+        asm volatile("" : "+s"(ta) : "s"(Ac[7]));
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const double2 a2 = sA2[u];
-          Ac[2 * u] = a2.x;
-          Ac[2 * u + 1] = a2.y;
-        }
+        for (int u = 0; u < 8; ++u) An[u] = Ag[ta + u];
+        __builtin_amdgcn_sched_barrier(0);
+        float *trow = tw + t8 * 4 * kTileRS + j;
         // rows l > lmax only feed output rows that are never stored
         if (tb8 <= tlast) {  // uniform: some ring starts in this group
 #pragma unroll
@@ -181,7 +248,7 @@ __global__ void __launch_bounds__(64 * NW)
               prv = cur;
               cur = nx;
             }
-            tw[(t8 * 8 + u) * kTileRS + j] = (float)cur;
+            trow[((u & 1) * 32 + (u >> 1)) * kTileRS] = (float)cur;
           }
         } else {
 #pragma unroll
@@ -189,33 +256,63 @@ __global__ void __launch_bounds__(64 * NW)
             const double nx = fma(Ac[u] * z, cur, -prv);
             prv = cur;
             cur = nx;
-            tw[(t8 * 8 + u) * kTileRS + j] = (float)cur;
+            trow[((u & 1) * 32 + (u >> 1)) * kTileRS] = (float)cur;
           }
         }
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      // contraction: even rows l0+hb*64+2i, odd rows +1; K = 32 steps of 2 rings
-      const int i = col;
-      const float *re = tw + (2 * i) * kTileRS + h * 32;
-      const float *ro = tw + (2 * i + 1) * kTileRS + h * 32;
 #pragma unroll
-      for (int s4 = 0; s4 < 8; ++s4) {
-        const float4 ae = *reinterpret_cast<const float4 *>(re + 4 * s4);
-        const float4 ao = *reinterpret_cast<const float4 *>(ro + 4 * s4);
-        acc[hb * 2 + 0] = mfma32(ae.x, xe[4 * s4 + 0], acc[hb * 2 + 0]);
-        acc[hb * 2 + 1] = mfma32(ao.x, xo[4 * s4 + 0], acc[hb * 2 + 1]);
-        acc[hb * 2 + 0] = mfma32(ae.y, xe[4 * s4 + 1], acc[hb * 2 + 0]);
-        acc[hb * 2 + 1] = mfma32(ao.y, xo[4 * s4 + 1], acc[hb * 2 + 1]);
-        acc[hb * 2 + 0] = mfma32(ae.z, xe[4 * s4 + 2], acc[hb * 2 + 0]);
-        acc[hb * 2 + 1] = mfma32(ao.z, xo[4 * s4 + 2], acc[hb * 2 + 1]);
-        acc[hb * 2 + 0] = mfma32(ae.w, xe[4 * s4 + 3], acc[hb * 2 + 0]);
-        acc[hb * 2 + 1] = mfma32(ao.w, xo[4 * s4 + 3], acc[hb * 2 + 1]);
+        for (int u = 0; u < 8; ++u) Ac[u] = An[u];
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    u32x4 xs[2][4][3];  // [E, O][K step][part]
+    // contraction: rows l0 + 64 hb + 2 i (E) and + 1 (O); K = 4 steps of 16
+    // rings, summed over the slice from zero and then added: products of a
+    // smooth spectrum's leading parts repeat from ring to ring, and so would
+    // the rounding of adding them to a long sum
+    auto contract = [&](f32x16 &ce, f32x16 &co) {
+      const float *rows = tw + col * kTileRS + h * 8;
+#pragma unroll
+      for (int par = 0; par < 2; ++par) {
+        f32x16 sum = {};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          u32x4 a[3];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const float4 v4 = *reinterpret_cast<const float4 *>(rows + par * 32 * kTileRS + 16 * s + 4 * i);
+            split3<true>(v4.x, v4.y, a, 2 * i);
+            split3<true>(v4.z, v4.w, a, 2 * i + 1);
+          }
+          mfma_split(a, xs[par][s], sum);
+        }
+        f32x16 &c = par ? co : ce;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) c[r] += sum[r];
+        __builtin_amdgcn_sched_barrier(0);  // one parity's operands at a time (registers)
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    // half blocks with no lambda are left out: every ring of the wave starts
+    // after the first (the recurrence state stays zero until its start), or
+    // every l of the second is beyond lmax (output rows that are never stored)
+    const bool first = tfirst < kSubL;
+    if (first) recurrence(0);
+#pragma unroll
+    for (int par = 0; par < 2; ++par)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) split3<true>(xf[par][8 * s + 2 * i], xf[par][8 * s + 2 * i + 1], xs[par][s], i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    if (first) contract(acc[0], acc[1]);
+    if (l0 + kSubL <= L) {
+      recurrence(kSubL);
+      contract(acc[2], acc[3]);
     }
   }
   // sum the waves' partial tiles, red[w][l - l0][col] (row stride
@@ -257,46 +354,6 @@ __global__ void __launch_bounds__(64 * NW)
       v.y += o.y;
     }
     *dst = v;
-  }
-}
-
-// FP32 products on the BF16 matrix cores.  An FP32 value is the sum of three
-// BF16 values, x = h + m + l with each part the rounding of what the ones
-// before it leave (8 bits each, 24 in all; exact down to the subnormal range
-// of l), and a product of two such values is taken as the six partial products
-// hh + hm + mh + hl + lh + mm; the three left out are below 2^-26 of it.  All
-// of them are exact in FP32 and are added in FP32 by the matrix core, 16 terms
-// of K to a rounding (the FP32 instruction: 2), so the sums are no further
-// from the exact ones than FP32 products' (random operands, relative l2
-// against FP64: 6.8e-7 for FP32 products, K 2048: 8.4e-7).  Six
-// v_mfma_f32_32x32x16_bf16 take 192 cycles for what eight
-// v_mfma_f32_32x32x2_f32 take 512, and the vector ALU issues beside them
-// (beside FP32 matrix instructions it does not: both use its multipliers).
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ f32x16 mfma_bf(u32x4 a, u32x4 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
-                                                  0, 0);
-}
-// the three BF16 parts of two values, `x0` in bits 0-15 (the words are opaque
-// to the compiler, which would round the low halves a second time by themselves)
-__device__ __forceinline__ void split3(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l) {
-  h = pack_bf16x2(x0, x1);
-  asm("" : "+v"(h));
-  const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
-  m = pack_bf16x2(r0, r1);
-  asm("" : "+v"(m));
-  l = pack_bf16x2(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
-}
-// c0 += a0 b, c1 += a1 b for operands in three parts, small products first and
-// alternating (no product waits for the one before it)
-__device__ __forceinline__ void mfma_split2(const u32x4 (&a0)[3], const u32x4 (&a1)[3], const u32x4 (&b)[3],
-                                            f32x16 &c0, f32x16 &c1) {
-  constexpr int ia[6] = {0, 2, 1, 0, 1, 0}, ib[6] = {2, 0, 1, 1, 0, 0};
-#pragma unroll
-  for (int k = 0; k < 6; ++k) {
-    c0 = mfma_bf(a0[ia[k]], b[ib[k]], c0);
-    c1 = mfma_bf(a1[ia[k]], b[ib[k]], c1);
   }
 }
 
@@ -436,8 +493,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NC == 1
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int par = 0; par < 2; ++par)
-          split3(lam[4 * i + par], lam[4 * i + 2 + par], w[par][0][2 * s + i], w[par][1][2 * s + i],
-                 w[par][2][2 * s + i]);
+          split3<false>(lam[4 * i + par], lam[4 * i + 2 + par], w[par], 2 * s + i);
 #pragma unroll
       for (int u = 0; u < 8; ++u) ac[u] = an[u];
     }
@@ -457,13 +513,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NC == 1
       for (int n = 0; n < NC; ++n) {
         u32x4 b[3];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          uint32_t bh, bm, bl;
-          split3(bf[n][par][2 * i], bf[n][par][2 * i + 1], bh, bm, bl);
-          b[0][i] = bh;
-          b[1][i] = bm;
-          b[2][i] = bl;
-        }
+        for (int i = 0; i < 4; ++i) split3<false>(bf[n][par][2 * i], bf[n][par][2 * i + 1], b, i);
         mfma_split2(a0, a1, b, acc[n][par], acc[n][2 + par]);
       }
     }

@@ -74,3 +74,43 @@ def test_synthesis_coefficient_range(shtx, scale):
     got = shtx.alm2map_raw(torch.tensor(alm, device="cuda"), nside, lmax).cpu().numpy().astype(np.float64)
     ref = sht.alm2map(alm.astype(np.complex128), nside, lmax)
     assert np.isfinite(got).all() and rel_l2(got / scale, ref / scale) <= TOL
+
+
+# item edges of the analysis: band limits that end inside the first and second
+# half of a block of 128 l, a block exactly full and one past it; fewer, as many
+# and more ring pairs than a slice of 64, with partial slices per wave; partial
+# channel groups
+@pytest.mark.parametrize("nside,lmax,batch", [(1, 2, 5), (8, 31, 17), (16, 47, 16), (32, 63, 5), (32, 64, 33),
+                                              (64, 127, 6), (64, 128, 16), (128, 301, 5)])
+def test_analysis_edges(shtx, nside, lmax, batch):
+    print("\n[case] analysis nside=%d lmax=%d B=%d" % (nside, lmax, batch), flush=True)
+    maps = synth.white_map(nside + lmax + batch, batch, 12 * nside * nside).astype(np.float32)
+    got = shtx.map2alm_raw(torch.tensor(maps, device="cuda"), lmax).cpu().numpy()
+    assert rel_l2(got, sht.map2alm(maps.astype(np.float64), lmax, nside)) <= TOL
+
+
+@pytest.mark.parametrize("nside,lmax,batch", [(64, 150, 5), (256, 300, 16)])
+def test_analysis_of_constant_maps(shtx, nside, lmax, batch):
+    """A constant map's products repeat from ring to ring and so do their
+    roundings: 24 of them (at most 2^-24 each) in the sum over a slice of 64
+    rings, then one per slice (8 at Nside 256), 32 x 2^-24 = 1.9e-6 at most."""
+    print("\n[case] analysis of constants nside=%d lmax=%d B=%d" % (nside, lmax, batch), flush=True)
+    c = (1.2345678 + 0.37 * np.arange(batch)).astype(np.float32)
+    maps = np.repeat(c[:, None], 12 * nside * nside, axis=1)
+    got = shtx.map2alm_raw(torch.tensor(maps, device="cuda"), lmax).cpu().numpy()
+    assert rel_l2(got, sht.map2alm(maps.astype(np.float64), lmax, nside)) <= 2e-6
+
+
+def test_analysis_keeps_channels_apart(shtx):
+    """An infinite and a NaN pixel stay in their channels."""
+    print("\n[case] analysis, inf and NaN channels", flush=True)
+    nside, lmax, B = 16, 40, 18
+    x = torch.tensor(synth.white_map(7, B, 12 * nside * nside).astype(np.float32), device="cuda")
+    want = shtx.map2alm_raw(x, lmax)
+    x[3, 100] = float("inf")
+    x[16, 5] = float("nan")
+    got = shtx.map2alm_raw(x, lmax)
+    keep = [b for b in range(B) if b not in (3, 16)]
+    assert torch.equal(got[keep], want[keep])
+    for b in (3, 16):  # (the imaginary parts of m = 0 are written as zero)
+        assert (~torch.isfinite(torch.view_as_real(got[b]))).any(dim=1).all()
