@@ -207,26 +207,34 @@ int status_of(hipError_t e) { return e == hipSuccess ? SHTX_OK : SHTX_ERR_HIP; }
 
 // Matrix-core Legendre kernels serve FP32 contraction from mfma_min_batch()
 // channels up (below that the 32-column matrix tiles are mostly padding and the
-// vector-ALU kernels are faster).  Analysis: 5.  Synthesis: 5, and 3 up to Nside
-// 256, where the vector-ALU kernels' launches per channel-group width and long
-// serial waves weigh more (matrix cores against vector ALUs: Nside 1024 L 2047
-// B 4 1.46 / 1.13 ms, B 5 1.48 / 1.72; Nside 512 L 1023 B 4 0.244 / 0.187,
-// B 5 0.234 / 0.301; Nside 256 L 511 B 2 0.047 / 0.045, B 3 0.048 / 0.091,
-// B 4 0.049 / 0.056; Nside 64 L 191 B 3 0.015 / 0.037).  SHTX_MFMA_MIN_BATCH
-// sets both.  SHTX_FORCE_VALU=1 in the environment selects the vector-ALU
-// kernels everywhere.  Both are read per call.
+// vector-ALU kernels are faster).  Analysis: 5, and 3 up to Nside 256, where the
+// vector-ALU path takes a launch for two channels and one for the third (matrix
+// cores against vector ALUs, ms: Nside 1024 L 2047 B 4 1.96 / 1.80, B 5
+// 2.02 / 2.49; Nside 512 L 1023 B 3 0.290 / 0.250, B 4 0.282 / 0.246; Nside 256
+// L 511 B 3 0.067 / 0.069, B 4 0.068 / 0.058; Nside 64 L 191 B 3 0.014 / 0.021).
+// Synthesis: 5, and from 3 up to Nside 256, where the vector-ALU kernels'
+// launches per channel-group width and long serial waves weigh more (Nside 1024
+// L 2047 B 4 1.46 / 1.13, B 5 1.48 / 1.72; Nside 512 L 1023 B 4 0.244 / 0.187,
+// B 5 0.234 / 0.301; Nside 256 L 511 B 2 0.047 / 0.045, B 3 0.048 / 0.091, B 4
+// 0.049 / 0.056; Nside 64 L 191 B 3 0.015 / 0.037).  SHTX_MFMA_MIN_BATCH sets
+// both.  SHTX_FORCE_VALU=1 in the environment selects the vector-ALU kernels
+// everywhere.  Both are read per call.
 int mfma_min_batch(bool synthesis, int nside) {
   const char *e = getenv("SHTX_MFMA_MIN_BATCH");
   return e ? atoi(e) : synthesis && nside <= 256 ? 3 : 5;
 }
-// FP64 transforms take the FP64 matrix cores from 3 channels for the
-// analysis and 5 for the synthesis (measured at Nside 1024: analysis 2.42 ms
-// against 3.84 ms on the vector ALUs at 4 channels, 2.40 against 1.94 at 2;
-// synthesis 2.30 against 2.36 at 5, 2.29 against 1.69 at 4; the 16-column
-// tiles hold 8 channels); SHTX_MFMA_MIN_BATCH sets both.
-int mfma64_min_batch(bool synthesis) {
+bool fwd_on_mfma(int B, int nside) {
+  return B >= mfma_min_batch(false, nside) || (B == 3 && nside <= 256 && !getenv("SHTX_MFMA_MIN_BATCH"));
+}
+// FP64 transforms take the FP64 matrix cores from 3 channels (4 from Nside 512)
+// for the analysis and 5 for the synthesis (analysis, matrix cores against
+// vector ALUs, ms: Nside 1024 L 2047 B 3 2.31 / 2.05, B 4 2.32 / 2.49; Nside 512
+// L 1023 B 3 0.353 / 0.318; Nside 256 L 511 B 3 0.078 / 0.083; synthesis at Nside
+// 1024 2.30 / 2.36 at 5, 2.29 / 1.69 at 4; the 16-column tiles hold 8 channels);
+// SHTX_MFMA_MIN_BATCH sets both.
+int mfma64_min_batch(bool synthesis, int nside) {
   const char *e = getenv("SHTX_MFMA_MIN_BATCH");
-  return e ? atoi(e) : synthesis ? 5 : 3;
+  return e ? atoi(e) : synthesis ? 5 : nside <= 256 ? 3 : 4;
 }
 bool force_valu() {
   const char *e = getenv("SHTX_FORCE_VALU");
@@ -241,13 +249,13 @@ template <typename T> hipError_t legendre_fwd(const Tables &tb, int B, const cpl
 }
 template <> hipError_t legendre_fwd<double>(const Tables &tb, int B, const double2 *XE, const double2 *XO,
                                             double2 *alm, double f0, double fm, int accum, hipStream_t st) {
-  if (B >= mfma64_min_batch(false) && mfma_fwd_supported(tb) && !force_valu())
+  if (B >= mfma64_min_batch(false, tb.nside) && mfma_fwd_supported(tb) && !force_valu())
     return launch_legendre_fwd_mfma64(tb, B, XE, XO, alm, f0, fm, accum, st);
   return launch_legendre_fwd_valu<double>(tb, B, XE, XO, alm, f0, fm, accum, st);
 }
 template <> hipError_t legendre_fwd<float>(const Tables &tb, int B, const float2 *XE, const float2 *XO, float2 *alm,
                                            double f0, double fm, int accum, hipStream_t st) {
-  if (B >= mfma_min_batch(false, tb.nside) && mfma_fwd_supported(tb) && !force_valu())
+  if (fwd_on_mfma(B, tb.nside) && mfma_fwd_supported(tb) && !force_valu())
     return launch_legendre_fwd_mfma(tb, B, XE, XO, alm, f0, fm, accum, st);
   return launch_legendre_fwd_valu<float>(tb, B, XE, XO, alm, f0, fm, accum, st);
 }
@@ -257,7 +265,7 @@ template <> hipError_t legendre_fwd<float>(const Tables &tb, int B, const float2
 // vector-ALU kernels' groups otherwise.
 template <typename T> bool inv_on_mfma(const Tables &tb, int B) {
   if (force_valu()) return false;
-  return sizeof(T) == 4 ? B >= mfma_min_batch(true, tb.nside) : B >= mfma64_min_batch(true);
+  return sizeof(T) == 4 ? B >= mfma_min_batch(true, tb.nside) : B >= mfma64_min_batch(true, tb.nside);
 }
 
 template <typename T> hipError_t legendre_inv(const Tables &tb, int B, const cplx<T> *ALMT, SynLayout lay,

@@ -584,13 +584,15 @@ hipError_t launch_legendre_inv_mfma(const Tables &tb, int B, const float2 *ALMT,
   const int nch = (tb.npairs + kInvRings - 1) / kInvRings;
   const int noct = (tb.lmax + 1 + 7) / 8;
   const int per_xcd = ((noct + 7) / 8) * 8 * nch;  // octets per XCD x 8 m x chunks
-  // pairs of 16-channel groups share a wave's recurrence; then one group
-  const int n32 = (B + 15) / 32;
+  // pairs of 16-channel groups share a wave's recurrence, then one group; where
+  // the waves do not fill the chip, each group has its own (B 17, whole call:
+  // Nside 64 L 127 54 us as a pair, 50 as two groups of FP32 products)
+  const int n32 = tb.npairs > 256 ? (B + 15) / 32 : 0;
   if (n32 > 0)
     hipLaunchKernelGGL(k_legendre_inv_mfma<2>, dim3(8 * per_xcd, n32), dim3(64), 0, st, tb, B, 0, tb.coefA, ALMT, lay,
                        GN, GS);
   if (32 * n32 < B)
-    hipLaunchKernelGGL(k_legendre_inv_mfma<1>, dim3(8 * per_xcd, 1), dim3(64), 0, st, tb, B, 32 * n32, tb.coefA, ALMT,
+    hipLaunchKernelGGL(k_legendre_inv_mfma<1>, dim3(8 * per_xcd, (B - 32 * n32 + 15) / 16), dim3(64), 0, st, tb, B, 32 * n32, tb.coefA, ALMT,
                        lay, GN, GS);
   return hipGetLastError();
 }

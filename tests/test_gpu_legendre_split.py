@@ -114,3 +114,19 @@ def test_analysis_keeps_channels_apart(shtx):
     assert torch.equal(got[keep], want[keep])
     for b in (3, 16):  # (the imaginary parts of m = 0 are written as zero)
         assert (~torch.isfinite(torch.view_as_real(got[b]))).any(dim=1).all()
+
+
+# the vector-ALU analysis at the edges of its rings per lane and workgroup
+# shapes (up to 128, 256, 1024 ring pairs and more), one and two channels,
+# against the oracle at the transforms' tolerances
+@pytest.mark.parametrize("nside,lmax,batch", [(1, 1, 1), (16, 20, 2), (64, 127, 1), (64, 129, 2), (128, 150, 1),
+                                              (128, 260, 2), (256, 300, 1), (512, 513, 3), (1024, 260, 1),
+                                              (1024, 140, 2)])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_vector_alu_analysis(shtx, monkeypatch, nside, lmax, batch, dtype):
+    print("\n[case] vector-ALU analysis nside=%d lmax=%d B=%d %s" % (nside, lmax, batch, dtype), flush=True)
+    monkeypatch.setenv("SHTX_FORCE_VALU", "1")
+    x = torch.tensor(synth.white_map(nside + lmax, batch, 12 * nside * nside), dtype=dtype)
+    got = shtx.map2alm_raw(x.cuda(), lmax).cpu().numpy()
+    ref = sht.map2alm(x.double().numpy(), lmax, nside)
+    assert rel_l2(got, ref) <= (1e-12 if dtype == torch.float64 else TOL)
