@@ -97,7 +97,7 @@ struct FftGeom {
   int NT, G, tq_off, bs_nb;
   size_t lds;
 };
-FftGeom fft_geometry(int nside, int mmax_bs, int batch, size_t csize);
+FftGeom fft_geometry(int nside, int mmax_bs, int batch, size_t csize, bool small);
 
 // Layout of the synthesis spectra g_m (Legendre output, ring FFT input):
 // element (p, c, m) at ((p ns + c/G) M + m) G + c%G, slices of G channels.

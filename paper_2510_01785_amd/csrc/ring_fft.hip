@@ -16,12 +16,14 @@
 // f_S (imaginary part).
 //
 // Spectra layout in the workspace: [ring pair p][m][batch], complex.
+#include <algorithm>
+
 #include "common.h"
 
 namespace shtx {
 
 constexpr int kFftOutMax = 16;    // complex values per thread per stage
-constexpr int kFftThreads = 512;  // threads per workgroup
+constexpr int kFftThreads = 512;  // threads per workgroup (128 or 256 for short rings: fft_geometry)
 
 // Index of logical element o in the LDS work buffer.  Transforms of length
 // >= 256 insert one padding slot every 16 elements, so that the stride-R
@@ -538,8 +540,10 @@ __device__ __forceinline__ void ring_dft(const Tables &tb, cplx<T> *buf, cplx<T>
 template <typename T> struct BsLayout {
   static constexpr int kLdsY1 = sizeof(T) == 8 ? 2 : 3;  // results kept in LDS when nb = 1
 };
-template <int NT> struct BsSlots {  // values of s < i per thread (i < kMaxNside)
-  static constexpr int value = (kMaxNside + NT - 1) / NT;
+// Values of s < i (over the channels of a call) per thread: the smaller
+// workgroups serve smaller rings (fft_geometry).
+template <int NT> struct BsSlots {
+  static constexpr int value = NT == 512 ? kMaxNside / 512 : NT == 256 ? kMaxNside / 256 : 2;
 };
 
 // Forward DFT of one channel of a ring of length n = 4i whose i has a prime
@@ -1199,7 +1203,8 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2)
 // lengths up to 4 * 2048; Bluestein rings use convolution lengths M < 2 nside.
 constexpr size_t kMaxLds = 160 * 1024;  // LDS of one gfx950 workgroup
 
-static FftGeom fft_geometry_nt(int nside, int mmax_bs, int batch, size_t csize, int NT, size_t lds_limit) {
+static FftGeom fft_geometry_nt(int nside, int mmax_bs, int batch, size_t csize, int NT, size_t lds_limit,
+                               int gmax) {
   FftGeom g{};
   const int nmax = 4 * nside;
   g.NT = NT;
@@ -1208,8 +1213,9 @@ static FftGeom fft_geometry_nt(int nside, int mmax_bs, int batch, size_t csize, 
   const int lds_cap = (int)((72 * 1024) / (nmax * csize));
   if (G > lds_cap) G = lds_cap;
   if (G > batch) G = batch;
-  if (G > 16) G = 16;
+  if (G > gmax) G = gmax;
   if (G < 1) G = 1;
+  G = (batch + (batch + G - 1) / G - 1) / ((batch + G - 1) / G);  // slices of equal width (5 channels: 3 + 2, not 4 + 1)
   g.G = G;
   size_t need = lds_elems((size_t)G * nmax);
   // octant root table of the largest power-of-two length used
@@ -1235,6 +1241,19 @@ static FftGeom fft_geometry_nt(int nside, int mmax_bs, int batch, size_t csize, 
   return g;
 }
 
+// Workgroup size and channel slice.  Up to Nside 256 a ring's work is short next
+// to the latency of its chain of loads, barriers and stages, so channels go to
+// workgroups of their own until these fill the chip three times over (16 waves
+// per CU in FP32, 8 in FP64), and the workgroups shrink (from 4 nside threads, at
+// most 512, to 128, or 256 at Nside 256) before they queue up; at Nside 256 from
+// 9 channels the chip is full with whole slices (B 64 282 / 334 against 296 /
+// 340).  Forward /
+// inverse, us, against one workgroup of 512 threads for all channels that fit:
+// Nside 32 L 95 FP32 B 3 24 / 29 -> 12 / 13, B 16 25 / 29 -> 13 / 14, B 64 25 / 29 ->
+// 22 / 24; Nside 64 L 191 B 3 27 / 31 -> 14 / 14, B 64 41 / 45 -> 32 / 35; Nside 128
+// L 301 B 5 40 / 38 -> 23 / 22, FP64 B 64 194 / 198 -> 128 / 122; Nside 256 L 767 B 5
+// 51 / 55 -> 41 / 43.  (NESTED maps keep the larger slices: `small` false.)
+//
 // FP64 transforms of 4 or more channels whose channel slice and Bluestein
 // sub-transforms fit a 256-thread stage run 256-thread workgroups with at
 // most half the LDS, two per CU (a 512-thread FP64 workgroup holds one
@@ -1242,11 +1261,23 @@ static FftGeom fft_geometry_nt(int nside, int mmax_bs, int batch, size_t csize, 
 // buffers, most of the LDS: one workgroup per CU).  Measured at Nside 1024,
 // B 16: forward 2.65 -> 2.50 ms, inverse 3.42 -> 2.91 ms; at one channel the
 // Bluestein rings' sub-transforms one at a time made the inverse 8% slower,
-// so smaller batches keep 512 threads.
-FftGeom fft_geometry(int nside, int mmax_bs, int batch, size_t csize) {
-  const FftGeom g = fft_geometry_nt(nside, mmax_bs, batch, csize, kFftThreads, kMaxLds);
+// so smaller batches keep 512 threads there; at Nside 512 they take 256 (B 1
+// 63 / 64 -> 52 / 52 us, B 3 177 / 182 -> 128 / 130).
+FftGeom fft_geometry(int nside, int mmax_bs, int batch, size_t csize, bool small) {
+  const int Rp = 2 * nside, slots = csize == 8 ? 4096 : 2048;  // waves resident on the chip
+  if (small && nside <= (batch <= 8 ? 256 : 128)) {
+    const int ntmin = nside <= 128 ? 128 : 256;
+    int NT = std::min(512, std::max(4 * nside, ntmin));
+    while (NT > ntmin && (long long)Rp * batch * (NT / 64) > slots) NT /= 2;
+    int gmax = 1;
+    while (gmax < 16 && (long long)Rp * ((batch + gmax - 1) / gmax) * (NT / 64) > 3 * slots) gmax *= 2;
+    return fft_geometry_nt(nside, mmax_bs, batch, csize, NT, kMaxLds, gmax);
+  }
+  if (small && nside == 512 && csize == 16 && batch < 4)
+    return fft_geometry_nt(nside, mmax_bs, batch, csize, 256, kMaxLds, 1);
+  const FftGeom g = fft_geometry_nt(nside, mmax_bs, batch, csize, kFftThreads, kMaxLds, 16);
   if (csize == 16 && batch >= 4 && (size_t)g.G * 4 * nside <= 256 * kFftOutMax && mmax_bs <= 256 * kFftOutMax) {
-    const FftGeom h = fft_geometry_nt(nside, mmax_bs, batch, csize, 256, kMaxLds / 2);
+    const FftGeom h = fft_geometry_nt(nside, mmax_bs, batch, csize, 256, kMaxLds / 2, 16);
     if (h.lds <= kMaxLds / 2 && h.G == g.G) return h;
   }
   return g;
@@ -1271,11 +1302,13 @@ template <typename K> hipError_t allow_lds(K kern, size_t lds) {
 template <typename TIn, typename T, typename TS>
 hipError_t launch_ring_fft_fwd(Tables tb, int B, const TIn *map, const double *wtab, double wscale,
                                const double *pixw, TS *XE, TS *XO, hipStream_t st, bool nested) {
-  const FftGeom g = fft_geometry(tb.nside, tb.mmax_bs, B, sizeof(cplx<T>));
+  const FftGeom g = fft_geometry(tb.nside, tb.mmax_bs, B, sizeof(cplx<T>), !nested);
   if (g.lds > kMaxLds) return hipErrorInvalidValue;
   auto kern = nested ? k_ring_fft_fwd<TIn, T, TS, true, kFftThreads> : k_ring_fft_fwd<TIn, T, TS, false, kFftThreads>;
+  if (g.NT == 256) kern = k_ring_fft_fwd<TIn, T, TS, false, 256>;
+  if (g.NT == 128) kern = k_ring_fft_fwd<TIn, T, TS, false, 128>;
   if constexpr (sizeof(T) == 8) {
-    if (g.NT == 256) kern = nested ? k_ring_fft_fwd<TIn, T, TS, true, 256> : k_ring_fft_fwd<TIn, T, TS, false, 256>;
+    if (g.NT == 256 && nested) kern = k_ring_fft_fwd<TIn, T, TS, true, 256>;
   }
   hipError_t e = allow_lds(kern, g.lds);
   if (e != hipSuccess) return e;
@@ -1288,12 +1321,11 @@ hipError_t launch_ring_fft_fwd(Tables tb, int B, const TIn *map, const double *w
 template <typename TOut, typename T>
 hipError_t launch_ring_fft_inv(Tables tb, int B, const cplx<T> *GN, const cplx<T> *GS, const TOut *sub, TOut *map,
                                hipStream_t st) {
-  const FftGeom g = fft_geometry(tb.nside, tb.mmax_bs, B, sizeof(cplx<T>));
+  const FftGeom g = fft_geometry(tb.nside, tb.mmax_bs, B, sizeof(cplx<T>), true);
   if (g.lds > kMaxLds) return hipErrorInvalidValue;
   auto kern = k_ring_fft_inv<TOut, T, kFftThreads>;
-  if constexpr (sizeof(T) == 8) {
-    if (g.NT == 256) kern = k_ring_fft_inv<TOut, T, 256>;
-  }
+  if (g.NT == 256) kern = k_ring_fft_inv<TOut, T, 256>;
+  if (g.NT == 128) kern = k_ring_fft_inv<TOut, T, 128>;
   hipError_t e = allow_lds(kern, g.lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(fft_grid(tb.npairs, B, g.G)), dim3(g.NT), g.lds, st, tb, B, g.G, g.tq_off,
