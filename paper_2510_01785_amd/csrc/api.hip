@@ -230,7 +230,9 @@ bool fwd_on_mfma(int B, int nside) {
 // for the analysis and 5 for the synthesis (analysis, matrix cores against
 // vector ALUs, ms: Nside 1024 L 2047 B 3 2.31 / 2.05, B 4 2.32 / 2.49; Nside 512
 // L 1023 B 3 0.353 / 0.318; Nside 256 L 511 B 3 0.078 / 0.083; synthesis at Nside
-// 1024 2.30 / 2.36 at 5, 2.29 / 1.69 at 4; the 16-column tiles hold 8 channels);
+// 512 L 1023 0.345 / 0.411 at 5, 0.347 / 0.294 at 4; the 16-column tiles hold 8
+// channels), and 3 for the synthesis up to Nside 128, whose vector-ALU path takes
+// two launches there (Nside 128 L 383 34 / 47 us, Nside 64 L 191 16 / 27 us);
 // SHTX_MFMA_MIN_BATCH sets both.
 int mfma64_min_batch(bool synthesis, int nside) {
   const char *e = getenv("SHTX_MFMA_MIN_BATCH");
@@ -265,7 +267,8 @@ template <> hipError_t legendre_fwd<float>(const Tables &tb, int B, const float2
 // vector-ALU kernels' groups otherwise.
 template <typename T> bool inv_on_mfma(const Tables &tb, int B) {
   if (force_valu()) return false;
-  return sizeof(T) == 4 ? B >= mfma_min_batch(true, tb.nside) : B >= mfma64_min_batch(true, tb.nside);
+  if (sizeof(T) == 4) return B >= mfma_min_batch(true, tb.nside);
+  return B >= mfma64_min_batch(true, tb.nside) || (B == 3 && tb.nside <= 128 && !getenv("SHTX_MFMA_MIN_BATCH"));
 }
 
 template <typename T> hipError_t legendre_inv(const Tables &tb, int B, const cplx<T> *ALMT, SynLayout lay,

@@ -484,14 +484,34 @@ hipError_t launch_legendre_fwd_valu(const Tables &tb, int B, const cplx<T> *XE, 
   return hipGetLastError();
 }
 
-template <typename T, int BG>
+template <typename T, int BG, int R>
 static void launch_inv_cfg(const Tables &tb, int B, int b0, int ngroups, const cplx<T> *ALMT, SynLayout lay,
                            cplx<T> *GN, cplx<T> *GS, hipStream_t st) {
-  constexpr int R = BG == 1 ? 4 : 2;  // ring pairs per lane
   const int nch = (tb.npairs + 64 * R - 1) / (64 * R);
   const int nm = (tb.lmax + 1 + 7) / 8;
   hipLaunchKernelGGL((k_legendre_inv_valu<T, BG, R>), dim3(8 * nm * nch, ngroups), dim3(64), 0, st, tb, B, b0,
                      ALMT, lay, GN, GS);
+}
+
+// Ring pairs per lane by the waves there are with one: more per lane share the
+// scalar loads and hide their latency, fewer shorten each wave's serial chain
+// when the waves do not fill the chip.  Measured, us, one / two / four per lane:
+// one channel FP64 Nside 64 L 191 14 / 16 / 19, Nside 256 L 767 44 / 50 / 63, Nside
+// 512 L 1535 214 / 170 / 197, Nside 1024 L 3071 1639 / 1194 / 1161 (FP32
+// 1278 / 1109 / 1233); two channels FP64 Nside 256 L 257 21 / 25 / 30, Nside 512
+// L 1535 331 / 254 / 269, Nside 1024 L 1025 294 / 229 / 219 (four channels, Nside 512
+// L 1535 773 / 584 / 530); FP32 four channels
+// Nside 256 L 767 78 / 87, Nside 512 L 513 72 / 66.
+template <typename T, int BG>
+static void launch_inv_groups(const Tables &tb, int B, int b0, int ngroups, const cplx<T> *ALMT, SynLayout lay,
+                              cplx<T> *GN, cplx<T> *GS, hipStream_t st) {
+  const long long waves = (long long)(tb.lmax + 1) * ((tb.npairs + 63) / 64) * ngroups;
+  if (waves < (BG == 1 ? 12288 : 7168)) return launch_inv_cfg<T, BG, 1>(tb, B, b0, ngroups, ALMT, lay, GN, GS, st);
+  if constexpr (sizeof(T) == 8) {
+    if (waves > (BG == 1 ? 50000 : tb.npairs >= 2048 ? 30000 : 45000))
+      return launch_inv_cfg<T, BG, 4>(tb, B, b0, ngroups, ALMT, lay, GN, GS, st);
+  }
+  launch_inv_cfg<T, BG, 2>(tb, B, b0, ngroups, ALMT, lay, GN, GS, st);
 }
 
 // Channel groups of 4 (FP32) or 2 (FP64), then 2 and 1 for the rest: the
@@ -501,13 +521,13 @@ hipError_t launch_legendre_inv_valu(const Tables &tb, int B, const cplx<T> *ALMT
                                     cplx<T> *GS, hipStream_t st) {
   constexpr int BGMAX = sizeof(T) == 8 ? 2 : 4;
   int b0 = 0;
-  if (B >= BGMAX) launch_inv_cfg<T, BGMAX>(tb, B, 0, B / BGMAX, ALMT, lay, GN, GS, st);  // one launch per width
+  if (B >= BGMAX) launch_inv_groups<T, BGMAX>(tb, B, 0, B / BGMAX, ALMT, lay, GN, GS, st);  // one launch per width
   b0 = B / BGMAX * BGMAX;
   if (BGMAX == 4 && b0 + 2 <= B) {
-    launch_inv_cfg<T, 2>(tb, B, b0, 1, ALMT, lay, GN, GS, st);
+    launch_inv_groups<T, 2>(tb, B, b0, 1, ALMT, lay, GN, GS, st);
     b0 += 2;
   }
-  if (b0 < B) launch_inv_cfg<T, 1>(tb, B, b0, 1, ALMT, lay, GN, GS, st);
+  if (b0 < B) launch_inv_groups<T, 1>(tb, B, b0, 1, ALMT, lay, GN, GS, st);
   return hipGetLastError();
 }
 

@@ -130,3 +130,17 @@ def test_vector_alu_analysis(shtx, monkeypatch, nside, lmax, batch, dtype):
     got = shtx.map2alm_raw(x.cuda(), lmax).cpu().numpy()
     ref = sht.map2alm(x.double().numpy(), lmax, nside)
     assert rel_l2(got, ref) <= (1e-12 if dtype == torch.float64 else TOL)
+
+
+# the vector-ALU synthesis with one, two and four ring pairs per lane (the
+# number of waves decides), partial lanes, every channel-group width
+@pytest.mark.parametrize("nside,lmax,batch", [(1, 1, 1), (16, 33, 2), (64, 65, 4), (128, 130, 7), (512, 900, 1),
+                                              (512, 600, 2), (1024, 520, 4), (1024, 2100, 1)])
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+def test_vector_alu_synthesis(shtx, monkeypatch, nside, lmax, batch, dtype):
+    print("\n[case] vector-ALU synthesis nside=%d lmax=%d B=%d %s" % (nside, lmax, batch, dtype), flush=True)
+    monkeypatch.setenv("SHTX_FORCE_VALU", "1")
+    alm = torch.tensor(synth.gaussian_alm(nside + lmax, batch, lmax, "lp10")).to(dtype)
+    got = shtx.alm2map_raw(alm.cuda(), nside, lmax).cpu().numpy()
+    ref = sht.alm2map(alm.numpy().astype(np.complex128), nside, lmax)
+    assert rel_l2(got, ref) <= (1e-12 if dtype == torch.complex128 else TOL)
