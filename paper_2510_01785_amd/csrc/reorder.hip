@@ -48,17 +48,17 @@ __device__ __forceinline__ uint32_t compact_even_bits(uint32_t v) {
   return v;
 }
 
-// bits 0, 1, 2, ... of v (v < 2^16) spread to bits 0, 2, 4, ...
-__device__ __forceinline__ uint32_t spread_bits(uint32_t v) {
-  v &= 0x0000ffffu;
-  v = (v | (v << 8)) & 0x00ff00ffu;
-  v = (v | (v << 4)) & 0x0f0f0f0fu;
-  v = (v | (v << 2)) & 0x33333333u;
-  v = (v | (v << 1)) & 0x55555555u;
+constexpr int kTileLog = 6;  // squares of up to 64 x 64 pixels
+
+// bits 0, 1, 2, ... of a coordinate inside a square (below 2^6) spread to bits
+// 0, 2, 4, ...
+__device__ __forceinline__ uint32_t spread6(int c) {
+  uint32_t v = (uint32_t)c;
+  v = (v | (v << 4)) & 0x30fu;
+  v = (v | (v << 2)) & 0x333u;
+  v = (v | (v << 1)) & 0x555u;
   return v;
 }
-
-constexpr int kTileLog = 6;  // squares of up to 64 x 64 pixels
 
 enum Kind { kRing = 0, kNest = 1, kFlat = 2 };
 
@@ -122,19 +122,49 @@ __device__ __forceinline__ Square square_of(uint32_t blk, int lgn, int lgt) {
   return s;
 }
 
+// Where the ring diagonals d = x + y of a square lie in RING order: for each,
+// the ring's first pixel - 1, the slot j of the diagonal's first pixel before
+// wrapping, and the ring's length.  One thread per diagonal, once per square.
+constexpr int kMaxDiag = 2 * (1 << kTileLog) - 1;
+__device__ __forceinline__ void diagonal_table(const Square &sq, int lgn, int lgt, uint4 *tab) {
+  const int N = 1 << lgn, T = 1 << lgt;
+  const uint32_t npix = 12u << (2 * lgn);
+  const int d = threadIdx.x;
+  if (d >= 2 * T - 1) return;
+  const int xmin = d < T ? 0 : d - T + 1;
+  const int i = sq.rf * N - (sq.X0 + sq.Y0 + d) - 1;  // ring, 1 .. 4N-1
+  int n, shift;
+  uint32_t start;
+  if (i < N) {  // north cap
+    n = i;
+    shift = 0;
+    start = 2u * (uint32_t)i * (uint32_t)(i - 1);
+  } else if (i > 3 * N) {  // south cap
+    n = 4 * N - i;
+    shift = 0;
+    start = npix - 2u * (uint32_t)n * (uint32_t)(n + 1);
+  } else {  // belt
+    n = N;
+    shift = (i - N) & 1;
+    start = 2u * (uint32_t)N * (uint32_t)(N - 1) + 4u * (uint32_t)N * (uint32_t)(i - N);
+  }
+  const int j0 = (sq.qf * n + (sq.X0 + xmin) - (sq.Y0 + d - xmin) + 1 + shift) >> 1;
+  tab[d] = make_uint4(start - 1u, (uint32_t)j0, 4u * (uint32_t)n, 0u);
+}
+
 // Visit every pixel of the square along its ring diagonals: fn(ring index in
 // the channel's map, local NESTED index).  The 256 threads take one diagonal
 // (or a pair of diagonals of 64 pixels in all) per wave step.
 template <typename Fn>
-__device__ __forceinline__ void ring_diagonals(const Square &sq, int lgn, int lgt, Fn fn) {
-  const int N = 1 << lgn, T = 1 << lgt;
-  const uint32_t npix = 12u << (2 * lgn);
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+__device__ __forceinline__ void ring_diagonals(const uint4 *tab, int lgt, Fn fn) {
+  const int T = 1 << lgt;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   // diagonals d = x + y of the square, lane k taking x = xmin(d) + k.  For
   // T = 64 the diagonals go in pairs of 64 pixels in all (d, 62 - d) and
   // (d, 190 - d), plus 31, 63 and 95 alone: 65 steps of one wave each;
   // smaller squares take one diagonal per step.
   const int nsteps = T == 64 ? 65 : 2 * T - 1;
+#pragma unroll 4
   for (int st = w; st < nsteps; st += 4) {
     int da = st, db = -1;
     if (T == 64) {
@@ -154,28 +184,13 @@ __device__ __forceinline__ void ring_diagonals(const Square &sq, int lgn, int lg
     if (lane >= la + lb) continue;
     const int d = lane < la ? da : db;
     const int k = lane < la ? lane : lane - la;
-    const int xmin = d < T ? 0 : d - T + 1;
-    const int i = sq.rf * N - (sq.X0 + sq.Y0 + d) - 1;  // ring, 1 .. 4N-1
-    int n, shift;
-    uint32_t start;
-    if (i < N) {  // north cap
-      n = i;
-      shift = 0;
-      start = 2u * (uint32_t)i * (uint32_t)(i - 1);
-    } else if (i > 3 * N) {  // south cap
-      n = 4 * N - i;
-      shift = 0;
-      start = npix - 2u * (uint32_t)n * (uint32_t)(n + 1);
-    } else {  // belt
-      n = N;
-      shift = (i - N) & 1;
-      start = 2u * (uint32_t)N * (uint32_t)(N - 1) + 4u * (uint32_t)N * (uint32_t)(i - N);
-    }
-    const int x = xmin + k, y = d - x;
-    int j = ((sq.qf * n + (sq.X0 + xmin) - (sq.Y0 + d - xmin) + 1 + shift) >> 1) + k;
-    if (j > 4 * n) j -= 4 * n;
-    if (j < 1) j += 4 * n;
-    fn(start + (uint32_t)(j - 1), spread_bits((uint32_t)x) | (spread_bits((uint32_t)y) << 1));
+    const int x = (d < T ? 0 : d - T + 1) + k, y = d - x;
+    const uint4 e = tab[d];
+    int j = (int)e.y + k;
+    const int n4 = (int)e.z;
+    j -= j > n4 ? n4 : 0;
+    j += j < 1 ? n4 : 0;
+    fn(e.x + (uint32_t)j, spread6(x) | (spread6(y) << 1));
   }
 }
 
@@ -193,7 +208,7 @@ __device__ __forceinline__ void flat_rows(const Square &sq, int lgn, int lgt, co
     const int c = c0 + (e & (T - 1)), r = r0 + (e >> lgt);
     int x, y;
     fo.xy(c, r, x, y);
-    const uint32_t li = spread_bits((uint32_t)(x - sq.X0)) | (spread_bits((uint32_t)(y - sq.Y0)) << 1);
+    const uint32_t li = spread6(x - sq.X0) | (spread6(y - sq.Y0) << 1);
     fn(base + (uint32_t)r * (uint32_t)N + (uint32_t)c, li);
   }
 }
@@ -202,6 +217,13 @@ __device__ __forceinline__ void flat_rows(const Square &sq, int lgn, int lgt, co
 // Src) into LDS, then written to `out` (layout Dst).  vec16: NESTED sides are
 // copied in 16-byte pieces (the host checks that the squares and both maps
 // allow it).
+//
+// Bound by the memory system and, for 4-byte and smaller elements, by the index
+// arithmetic.  Nside 1024 B 16, NESTED -> RING / RING -> NESTED, us: with each
+// lane working out its diagonal's ring FP32 575 / 473, BF16 380 / 413, FP64
+// 881 / 921; from a table per square, and the squares of one XCD contiguous,
+// 437 / 437, 275 / 365, 703 / 883 (the table alone: FP32 566 / 430).  Two FP32
+// channels per workgroup (indices computed once, 32 KB of LDS) 437 / 627.
 template <typename E, int Src, int Dst>
 __global__ void __launch_bounds__(256) k_reorder(int lgn, int lgt, int B, int vec16, FlatOrient fsrc, FlatOrient fdst,
                                                  const E *__restrict__ in, E *__restrict__ out) {
@@ -209,8 +231,17 @@ __global__ void __launch_bounds__(256) k_reorder(int lgn, int lgt, int B, int ve
   E *tile = reinterpret_cast<E *>(smem_raw);  // T*T values in local NESTED order
   const int TT = 1 << (2 * lgt);
   const uint32_t npix = 12u << (2 * lgn);
-  const Square sq = square_of(blockIdx.x, lgn, lgt);
+  // consecutive workgroups go to the eight XCDs in turn: each XCD takes one
+  // contiguous part of the squares, so that the neighbours that share the
+  // 128-byte lines at the ends of their runs meet in one L2
+  const uint32_t blk = (gridDim.x & 7) == 0 ? (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+  const Square sq = square_of(blk, lgn, lgt);
   const int tid = threadIdx.x;
+  __shared__ uint4 tab[kMaxDiag];
+  if (Src == kRing || Dst == kRing) {
+    diagonal_table(sq, lgn, lgt, tab);
+    if (Src == kRing) __syncthreads();  // (else the barrier below)
+  }
   for (int b = blockIdx.y; b < B; b += gridDim.y) {  // one channel per workgroup (row of the grid)
     const size_t o = (size_t)b * npix;
     const E *src = in + o;
@@ -226,7 +257,7 @@ __global__ void __launch_bounds__(256) k_reorder(int lgn, int lgt, int B, int ve
     } else if (Src == kFlat) {
       flat_rows(sq, lgn, lgt, fsrc, [&](uint32_t g, uint32_t li) { tile[li] = src[g]; });
     } else {
-      ring_diagonals(sq, lgn, lgt, [&](uint32_t g, uint32_t li) { tile[li] = src[g]; });
+      ring_diagonals(tab, lgt, [&](uint32_t g, uint32_t li) { tile[li] = src[g]; });
     }
     __syncthreads();
     if (Dst == kNest) {
@@ -240,7 +271,7 @@ __global__ void __launch_bounds__(256) k_reorder(int lgn, int lgt, int B, int ve
     } else if (Dst == kFlat) {
       flat_rows(sq, lgn, lgt, fdst, [&](uint32_t g, uint32_t li) { dst[g] = tile[li]; });
     } else {
-      ring_diagonals(sq, lgn, lgt, [&](uint32_t g, uint32_t li) { dst[g] = tile[li]; });
+      ring_diagonals(tab, lgt, [&](uint32_t g, uint32_t li) { dst[g] = tile[li]; });
     }
     __syncthreads();
   }
