@@ -51,6 +51,10 @@ __host__ __device__ inline size_t roots_offset(int i) {
 // transformed with Bluestein's chirp-z algorithm (Eq. (17)-(23)) on a
 // power-of-two length; the others with mixed radix 4/2/3/5/7/11/13.
 constexpr int kMaxDirectPrime = 13;
+// Prime factors that the ring FFT's register butterflies take (ring_fft.hip); ring
+// pairs within them that also have a chirp carry kButterflyRing in rp_M.
+constexpr int kMaxButterflyPrime = 23;
+constexpr int kButterflyRing = 1 << 30;
 
 __host__ __device__ inline int largest_odd_prime(int i) {
   while ((i & 1) == 0 && i > 0) i >>= 1;
@@ -149,7 +153,7 @@ constexpr size_t kCoefPadTable = kBlockL + 8;
 // Byte offsets of the pieces of the resident table buffer.
 struct TableOffsets {
   size_t rp_n, rp_sN, rp_sS, rp_p0n, rp_p0d;  // int32 [Rp]
-  size_t rp_M, rp_bsoff;                      // int32 [Rp]: Bluestein length (0: mixed radix), offset
+  size_t rp_M, rp_bsoff;                      // int32 [Rp]: Bluestein length (0: mixed radix; kButterflyRing), offset
   size_t rp_z, rp_sth, rp_w;                  // double [Rp]
   size_t coefA, coefC;                        // double [nalm + kCoefPadTable], zero padding
   size_t seed_l;                              // int32 [(L+1) * Rp]

@@ -375,8 +375,186 @@ __device__ __forceinline__ void fft_p2(cplx<T> *buf, int logn, int G, int pad, c
   else if (rem == 3) stage_p2<T, NT, 8>(buf, logn, G, logp, pad, tq, fz, fi, fout);
 }
 
-// Mixed-radix stages for ring lengths n = 4i with odd factors <= 13 (short
-// polar rings): twiddles from the ring's full root table in global memory.
+// cos(2 pi j / R) and sin(2 pi j / R) at compile time: the angle reduced to at
+// most pi / 4 in integers, then the Taylor series.
+constexpr double kPi = 3.14159265358979323846;
+constexpr double series_cos(double x) {
+  double t = 1.0, s = 1.0;
+  for (int k = 1; k < 12; ++k) {
+    t *= -x * x / ((2 * k - 1) * (2 * k));
+    s += t;
+  }
+  return s;
+}
+constexpr double series_sin(double x) {
+  double t = x, s = x;
+  for (int k = 1; k < 12; ++k) {
+    t *= -x * x / ((2 * k) * (2 * k + 1));
+    s += t;
+  }
+  return s;
+}
+constexpr double cos_turn(int j, int R) {  // 0 <= j < R
+  if (2 * j > R) return cos_turn(R - j, R);
+  if (4 * j > R) return -cos_turn(R - 2 * j, 2 * R);
+  return 8 * j > R ? series_sin(kPi * (R - 4 * j) / (2.0 * R)) : series_cos(2 * kPi * j / R);
+}
+constexpr double sin_turn(int j, int R) {
+  if (2 * j > R) return -sin_turn(R - j, R);
+  if (4 * j > R) return sin_turn(R - 2 * j, 2 * R);
+  return 8 * j > R ? series_cos(kPi * (R - 4 * j) / (2.0 * R)) : series_sin(2 * kPi * j / R);
+}
+// both for every j < R, folded into the unrolled butterflies
+template <int R> struct Turns {
+  double c[R], s[R];
+  constexpr Turns() : c{}, s{} {
+    for (int j = 0; j < R; ++j) {
+      c[j] = cos_turn(j, R);
+      s[j] = sin_turn(j, R);
+    }
+  }
+};
+
+// Mixed-radix Stockham stage of radix R and span p for ring lengths n = 4i with
+// prime factors up to kMaxButterflyPrime, a butterfly per thread in registers:
+//   y[(i - k) R + k + q p] = sum_r x[i + r n/R] w^{r k n/(R p)} exp(-2 pi i r q/R),
+// k = i mod p; twiddles from the ring's full root table in global memory, none
+// in the first stage (p = 1).  All inputs are read before the barrier.  For odd
+// R the outputs q and R - q are A -+ i B with A = x_0 + sum_r (x_r + x_{R-r})
+// cos(2 pi q r/R), B = sum_r (x_r - x_{R-r}) sin(2 pi q r/R), r up to
+// (R - 1)/2: R - 1 real products per output with constant factors, where a sum
+// per output with roots from memory takes some 12 R instructions and a Bluestein
+// ring about 570 per sample.  The kernels issue vector instructions in two thirds
+// of their time; those of Nside 1024 B 16 fell from 4.15e8 to 3.7e8 (FP32 analysis).
+// us, sums per output and Bluestein above 13 -> butterflies up to 13 / 19 / 23 / 31
+// (31 spills): FP32 Nside 1024 B 16 analysis 1040 -> 987 / 966 / 961 / 945, synthesis
+// 1311 -> 1313 / 1252 / 1262 / 1266; Nside 256 B 64 299 -> 269 / 257 / 256 / 259, 360 ->
+// 337 / 314 / 305 / 306; FP64 Nside 512 B 8 250 -> 243 / 237 / 235 / 251, 290 -> 281 /
+// 267 / 265 / 259.
+template <typename T, int NT, int R>
+__device__ __forceinline__ void stage_mix(cplx<T> *buf, int n, int G, int p, int pad,
+                                          const cplx<T> *__restrict__ roots) {
+  using C = cplx<T>;
+  constexpr int NB = (kFftOutMax + R - 1) / R;
+  constexpr int H = (R - 1) / 2;
+  // opaque: the divisions of every radix, hoisted to the kernel entry, would spill
+  asm volatile("" : "+s"(n), "+s"(p));
+  const int Tq = n / R;
+  const int nb = G * Tq;
+  const int step = Tq / p;
+  const FastDiv dq(Tq), dp(p);
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  C v[NB][R];
+#pragma unroll
+  for (int s = 0; s < NB; ++s) {
+    const int b = tid + s * NT;
+    if (b < nb) {
+      const int c = dq.quo(b), i = dq.rem(b, c);
+      const int ib = c * n + i;
+      if (p > 1) {
+        const int e = dp.rem(i, dp.quo(i)) * step;
+        v[s][0] = buf[lidx(ib, pad)];
+#pragma unroll
+        for (int r0 = 1; r0 < R; r0 += 8) {
+          C w[8];
+#pragma unroll
+          for (int r = r0; r < R && r < r0 + 8; ++r) w[r - r0] = roots[r * e];
+#pragma unroll
+          for (int r = r0; r < R && r < r0 + 8; ++r) v[s][r] = cmul(buf[lidx(ib + r * Tq, pad)], w[r - r0]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[s][r] = buf[lidx(ib + r * Tq, pad)];
+      }
+      if constexpr (R % 2 == 0) {
+        dftR<C, R>(v[s]);
+      } else {
+#pragma unroll
+        for (int r = 1; r <= H; ++r) {
+          const C a = v[s][r], d = v[s][R - r];
+          v[s][r] = cadd(a, d);
+          v[s][R - r] = csub(a, d);
+        }
+      }
+    }
+  }
+  __syncthreads();
+  asm volatile("" : "+v"(tid));
+#pragma unroll
+  for (int s = 0; s < NB; ++s) {
+    const int b = tid + s * NT;
+    if (b < nb) {
+      const int c = dq.quo(b), i = dq.rem(b, c);
+      const int k = dp.rem(i, dp.quo(i));
+      const int ob = c * n + (i - k) * R + k;
+      if constexpr (R % 2 == 0) {
+#pragma unroll
+        for (int q = 0; q < R; ++q) buf[lidx(ob + q * p, pad)] = v[s][q];
+      } else {
+        constexpr Turns<R> w;
+        C t = v[s][0];
+#pragma unroll
+        for (int r = 1; r <= H; ++r) t = cadd(t, v[s][r]);
+        buf[lidx(ob, pad)] = t;
+#pragma unroll
+        for (int q = 1; q <= H; ++q) {
+          C A = v[s][0], B = cmk<C>(0, 0);
+#pragma unroll
+          for (int r = 1; r <= H; ++r) {
+            const T cs = (T)w.c[q * r % R], sn = (T)w.s[q * r % R];
+            A.x = fma(v[s][r].x, cs, A.x);
+            A.y = fma(v[s][r].y, cs, A.y);
+            B.x = fma(v[s][R - r].x, sn, B.x);
+            B.y = fma(v[s][R - r].y, sn, B.y);
+          }
+          buf[lidx(ob + q * p, pad)] = cmk<C>(A.x + B.y, A.y - B.x);
+          buf[lidx(ob + (R - q) * p, pad)] = cmk<C>(A.x - B.y, A.y + B.x);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// Mixed-radix Stockham FFT of G channels of length n = 4i: the odd prime factors
+// first (the largest without twiddles), then the power-of-two part in radix 16, 8,
+// 4 or 2.
+template <typename T, int NT>
+__device__ __forceinline__ void fft_mixed(cplx<T> *buf, int n, int G, int pad, const cplx<T> *__restrict__ roots) {
+  int rem = n >> __builtin_ctz(n), p = 1;
+#define SHTX_ODD_STAGE(R)                         \
+  while (rem % R == 0) {                          \
+    stage_mix<T, NT, R>(buf, n, G, p, pad, roots); \
+    p *= R;                                       \
+    rem /= R;                                     \
+  }
+  SHTX_ODD_STAGE(23)
+  SHTX_ODD_STAGE(19)
+  SHTX_ODD_STAGE(17)
+  SHTX_ODD_STAGE(13)
+  SHTX_ODD_STAGE(11)
+  SHTX_ODD_STAGE(7)
+  SHTX_ODD_STAGE(5)
+  SHTX_ODD_STAGE(3)
+#undef SHTX_ODD_STAGE
+  rem = n & -n;
+  while (rem >= 16) {
+    stage_mix<T, NT, 16>(buf, n, G, p, pad, roots);
+    p *= 16;
+    rem >>= 4;
+  }
+  if (rem == 8) stage_mix<T, NT, 8>(buf, n, G, p, pad, roots);
+  else if (rem == 4) stage_mix<T, NT, 4>(buf, n, G, p, pad, roots);
+  else if (rem == 2) stage_mix<T, NT, 2>(buf, n, G, p, pad, roots);
+}
+
+// The stages of analyses with BF16 spectra, lengths 4i with odd factors up to
+// kMaxDirectPrime: a value that the butterflies' other rounding takes across a BF16
+// boundary moves by 2^-8 (Nside 128 .. 1024, some hundred calls: up to 5e-3 of the
+// coefficients' scale), so these spectra keep the sums they have.
 // Radix-4/2 stage (span p):
 template <typename T, int NT, int R>
 __device__ __forceinline__ void stage_mix_p2(cplx<T> *buf, int n, int G, int p, int pad,
@@ -480,7 +658,7 @@ __device__ __forceinline__ void stage_odd(cplx<T> *buf, int n, int G, int p, int
 // the power-of-two part, one radix-2 stage if needed, then one direct stage
 // per remaining odd prime factor (all <= kMaxDirectPrime on this path).
 template <typename T, int NT>
-__device__ __forceinline__ void fft_mixed(cplx<T> *buf, int n, int G, int pad, const cplx<T> *__restrict__ roots) {
+__device__ __forceinline__ void fft_mixed_direct(cplx<T> *buf, int n, int G, int pad, const cplx<T> *__restrict__ roots) {
   int rem = n, p = 1;
   while ((rem & 3) == 0) {
     stage_mix_p2<T, NT, 4>(buf, n, G, p, pad, roots);
@@ -516,12 +694,14 @@ __device__ __forceinline__ void load_octant(cplx<T> *tq, const cplx<T> *__restri
 // layout lidx(., pad)); tq is LDS space for an octant root table.  Every
 // thread of the workgroup calls this (it synchronises internally).  Ring
 // lengths with a power-of-two part only take radix-16 Stockham stages, the
-// others (prime factors <= kMaxDirectPrime) mixed-radix stages.
-template <typename T, int NT>
+// others mixed-radix stages (DIRECT: the ones of fft_mixed_direct).
+template <typename T, int NT, bool DIRECT>
 __device__ __forceinline__ void ring_dft(const Tables &tb, cplx<T> *buf, cplx<T> *tq, int n, int gc, int pad,
                                          bool tq_ready) {
   if (n & (n - 1)) {
-    fft_mixed<T, NT>(buf, n, gc, pad, TabOf<T>::roots(tb) + roots_offset(n >> 2));
+    const cplx<T> *roots = TabOf<T>::roots(tb) + roots_offset(n >> 2);
+    if constexpr (DIRECT) fft_mixed_direct<T, NT>(buf, n, gc, pad, roots);
+    else fft_mixed<T, NT>(buf, n, gc, pad, roots);
     return;
   }
   if (!tq_ready) {
@@ -667,6 +847,11 @@ __device__ __forceinline__ void ring_dft_bs4(const Tables &tb, int p, int M, int
     }
   }
   __syncthreads();
+}
+
+// Convolution length of a ring (0: mixed radix) from its table entry.
+template <bool DIRECT> __device__ __forceinline__ int convolution_len(int e) {
+  return DIRECT ? e & ~kButterflyRing : e & kButterflyRing ? 0 : e;
 }
 
 // Channels of a Bluestein ring per call of ring_dft_bs4: several when all
@@ -852,7 +1037,8 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2)
   const T w = (T)(wtab ? wtab[p] * wscale : wscale);
   const int num = tb.rp_p0n[p];  // phase numerator (the denominator is n when num = 1)
   const size_t npix = (size_t)tb.npix;
-  const int Mbs = tb.rp_M[p];
+  constexpr bool kDirect = std::is_same_v<TS, uint32_t>;
+  const int Mbs = convolution_len<kDirect>(tb.rp_M[p]);
   const int pad = Mbs == 0 && n >= kPadMin;  // Bluestein rings leave their DFT unpadded
   const int Gp = Mbs ? bs_channels<NT>(G, bs_nb, Mbs, n, tq_off) : G;
   const int nq = n >> 2;  // quads of pixels per ring
@@ -910,7 +1096,7 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2)
         }
       }
       __syncthreads();
-      ring_dft<T, NT>(tb, buf, tq, n, gc, pad, b0 != bg0);
+      ring_dft<T, NT, kDirect>(tb, buf, tq, n, gc, pad, b0 != bg0);
     }
     // E/O spectra for m = 0..L; one phase per m, channels contiguous
     const size_t obase = (size_t)p * M * B + b0;
@@ -972,7 +1158,7 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2)
   const int L = tb.lmax, M = L + 1;
   const int num = tb.rp_p0n[p];  // phase numerator (the denominator is n when num = 1)
   const size_t npix = (size_t)tb.npix;
-  const int Mbs = tb.rp_M[p];
+  const int Mbs = convolution_len<false>(tb.rp_M[p]);
   const int pad = Mbs == 0 && n >= kPadMin;  // Bluestein rings leave their DFT unpadded
   const int Gp = Mbs ? bs_channels<NT>(G, bs_nb, Mbs, n, tq_off) : G;
   int tid = threadIdx.x;
@@ -1162,7 +1348,7 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2)
         }
       }
       __syncthreads();
-      ring_dft<T, NT>(tb, buf, tq, n, gc, pad, b0 != bg0);
+      ring_dft<T, NT, false>(tb, buf, tq, n, gc, pad, b0 != bg0);
     }
     // IDFT(h) = conj(F): f_N = F.x, f_S = -F.y; four consecutive pixels per
     // item (ring starts and lengths are multiples of 4 pixels)

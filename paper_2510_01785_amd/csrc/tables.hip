@@ -50,7 +50,7 @@ __global__ void k_ring_pairs(int N, int *rp_n, int *rp_sN, int *rp_sS, int *p0n,
     M = bluestein_len(i);
     for (int j = 1; j < i; ++j) off += bluestein_len(j);
   }
-  rp_M[p] = M;
+  rp_M[p] = M && largest_odd_prime(i) <= kMaxButterflyPrime ? M | kButterflyRing : M;
   rp_bsoff[p] = off;
   rp_n[p] = n;
   rp_sN[p] = sN;
