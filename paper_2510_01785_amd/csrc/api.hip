@@ -42,8 +42,8 @@ hipError_t launch_legendre_fwd_mfma64(const Tables &, int, const double2 *, cons
                                       int, hipStream_t);
 hipError_t launch_legendre_inv_mfma64(const Tables &, int, const double2 *, SynLayout, double2 *, double2 *,
                                       hipStream_t);
-template <typename T, typename TI>
-hipError_t launch_alm_in(int, int, int, const cplx<TI> *, const double *, cplx<T> *, double, double, double,
+template <typename T>
+hipError_t launch_alm_in(int, int, int, const cplx<T> *, const double *, cplx<T> *, double, double, double,
                          hipStream_t);
 
 namespace {
@@ -346,7 +346,7 @@ int run_synthesis(const Tables &tb, int B, const cplx<T> *alm, TOut *map, double
     StageTimer t(kStAlmIn, st);
     const int gmax = mfma ? B : sizeof(T) == 8 ? 2 : 4;
     const double half = mfma && sizeof(T) == 4 ? 0.5 : 1.0;  // the FP32 matrix-core kernel doubles its sums
-    e = launch_alm_in<T, T>(tb.lmax, B, gmax, alm, tb.coefC, w.almt, half * s, f0, fm, st);
+    e = launch_alm_in<T>(tb.lmax, B, gmax, alm, tb.coefC, w.almt, half * s, f0, fm, st);
   }
   if (e != hipSuccess) return SHTX_ERR_HIP;
   {
