@@ -152,7 +152,8 @@ constexpr size_t kCoefPadTable = kBlockL + 8;
 
 // Byte offsets of the pieces of the resident table buffer.
 struct TableOffsets {
-  size_t rp_n, rp_sN, rp_sS, rp_p0n, rp_p0d;  // int32 [Rp]
+  size_t rp_n, rp_sN, rp_sS, rp_p0n;          // int32 [Rp]
+  size_t rp_mtop;                             // int32 [Rp]: 1 + the largest m with a stored seed
   size_t rp_M, rp_bsoff;                      // int32 [Rp]: Bluestein length (0: mixed radix; kButterflyRing), offset
   size_t rp_z, rp_sth, rp_w;                  // double [Rp]
   size_t coefA, coefC;                        // double [nalm + kCoefPadTable], zero padding
@@ -193,7 +194,7 @@ inline TableOffsets table_offsets(int nside, int lmax) {
   o.rp_sN = take(Rp * 4);
   o.rp_sS = take(Rp * 4);
   o.rp_p0n = take(Rp * 4);
-  o.rp_p0d = take(Rp * 4);
+  o.rp_mtop = take(Rp * 4);
   o.rp_M = take(Rp * 4);
   o.rp_bsoff = take(Rp * 4);
   o.rp_z = take(Rp * 8);
@@ -225,7 +226,7 @@ inline TableOffsets table_offsets(int nside, int lmax) {
 
 struct Tables {
   int nside, lmax, npairs, npix, mmax_bs, nitems;
-  const int *rp_n, *rp_sN, *rp_sS, *rp_p0n, *rp_p0d, *rp_M, *rp_bsoff;
+  const int *rp_n, *rp_sN, *rp_sS, *rp_p0n, *rp_mtop, *rp_M, *rp_bsoff;
   const double *rp_z, *rp_sth, *rp_w;
   const double *coefA, *coefC;
   const int *seed_l;
@@ -255,7 +256,7 @@ inline Tables tables_view(const void *base, int nside, int lmax) {
   t.rp_sN = reinterpret_cast<const int *>(b + o.rp_sN);
   t.rp_sS = reinterpret_cast<const int *>(b + o.rp_sS);
   t.rp_p0n = reinterpret_cast<const int *>(b + o.rp_p0n);
-  t.rp_p0d = reinterpret_cast<const int *>(b + o.rp_p0d);
+  t.rp_mtop = reinterpret_cast<const int *>(b + o.rp_mtop);
   t.rp_M = reinterpret_cast<const int *>(b + o.rp_M);
   t.rp_bsoff = reinterpret_cast<const int *>(b + o.rp_bsoff);
   t.rp_z = reinterpret_cast<const double *>(b + o.rp_z);

@@ -340,6 +340,15 @@ __global__ void __launch_bounds__(64)
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) wlv = min(wlv, __shfl_xor(wlv, o));
   const int wl = __builtin_amdgcn_readfirstlane(wlv);
+  if (wl > L) {
+    bool none = true;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int p = chunk * 64 * R + 64 * r + j;
+      none &= p >= Rp || m >= tb.rp_mtop[p];
+    }
+    if (__all(none)) return;  // zero spectra, which the ring FFT does not read
+  }
   const int aoff = m * (2 * L + 1 - m) / 2;  // alm_idx(m, m, L) - m
   const cdouble *A = (const cdouble *)tb.coefA + aoff;
   // a[l][b] (re, im) of this channel group, stored [idx][BG] (chan_group):

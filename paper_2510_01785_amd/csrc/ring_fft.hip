@@ -1155,7 +1155,12 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2)
   const int n = tb.rp_n[p];
   const int sN = tb.rp_sN[p], sS = tb.rp_sS[p];
   const bool equator = (sN == sS);
-  const int L = tb.lmax, M = L + 1;
+  const int M = tb.lmax + 1;
+  // From mt on the ring's spectra are zero (a third of them, toward the poles):
+  // neither stored by the Legendre step nor read here.  Nside 1024 L 2047 B 16 FP32
+  // 1265 -> 1048 us, Nside 256 L 767 B 64 308 -> 247, Nside 512 L 1023 B 8 FP64
+  // 264 -> 237, Nside 2048 L 4095 B 1 FP64 880 -> 801.
+  const int mt = tb.rp_mtop[p];
   const int num = tb.rp_p0n[p];  // phase numerator (the denominator is n when num = 1)
   const size_t npix = (size_t)tb.npix;
   const int Mbs = convolution_len<false>(tb.rp_M[p]);
@@ -1177,11 +1182,11 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2)
   auto fold_load = [&](const C *gn, const C *gs, int k, int c, C &pn, C &ps, C &qn, C &qs) {
     const int m1 = k, m2 = (k == 0) ? n : n - k;
     pn = ps = qn = qs = cmk<C>(0, 0);
-    if (m1 < M) {
+    if (m1 < mt) {
       pn = gn[(size_t)m1 * B + c];
       if (!equator) ps = gs[(size_t)m1 * B + c];
     }
-    if (m2 < M) {
+    if (m2 < mt) {
       qn = gn[(size_t)m2 * B + c];
       if (!equator) qs = gs[(size_t)m2 * B + c];
     }
@@ -1193,7 +1198,7 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2)
     cn = cmk<C>(0, 0);
     cs = cmk<C>(0, 0);
     const int m1 = k, m2 = (k == 0) ? n : n - k;  // both below 2n
-    if (m1 < M) {
+    if (m1 < mt) {
       const C ph = rph.plus(m1);
       cn = cmul(pn, ph);
       cs = cmul(ps, ph);
@@ -1202,17 +1207,17 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2)
         cs.y = 0;
       }
     }
-    if (m2 < M) {
+    if (m2 < mt) {
       const C ph = rph.plus(m2);
       cn = cadd(cn, cconj(cmul(qn, ph)));
       cs = cadd(cs, cconj(cmul(qs, ph)));
     }
     // further aliases m + t n: m mod 2n alternates between m and m + n
-    for (int m = m1 + n, mm = m1 + n; m < M; m += n, mm = mm >= n ? mm - n : mm + n) {
+    for (int m = m1 + n, mm = m1 + n; m < mt; m += n, mm = mm >= n ? mm - n : mm + n) {
       cn = cadd(cn, phased(gn + c, m, mm));
       if (!equator) cs = cadd(cs, phased(gs + c, m, mm));
     }
-    for (int m = m2 + n, mm = m2 + n >= 2 * n ? m2 - n : m2 + n; m < M;
+    for (int m = m2 + n, mm = m2 + n >= 2 * n ? m2 - n : m2 + n; m < mt;
          m += n, mm = mm >= n ? mm - n : mm + n) {
       cn = cadd(cn, cconj(phased(gn + c, m, mm)));
       if (!equator) cs = cadd(cs, cconj(phased(gs + c, m, mm)));
@@ -1234,7 +1239,7 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2)
     if (r == 0) {
       C pn, ps, qn, qs;
       fold_load(gn, gs, k, c, pn, ps, qn, qs);
-      if (m1 < M) {
+      if (m1 < mt) {
         const C ph = rph.plus(m1);
         cn = cmul(pn, ph);
         cs = cmul(ps, ph);
@@ -1243,7 +1248,7 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2)
           cs.y = 0;
         }
       }
-      if (m2 < M) {
+      if (m2 < mt) {
         const C ph = rph.plus(m2);
         cn = cadd(cn, cconj(cmul(qn, ph)));
         cs = cadd(cs, cconj(cmul(qs, ph)));
@@ -1255,7 +1260,7 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2)
       C an = cmk<C>(0, 0), as = cmk<C>(0, 0);
       const int mm = m1 + (t0 & 1) * n;  // m mod 2n (the same for every t of this lane)
 #pragma unroll 4
-      for (int m = m1 + t0 * n; m < M; m += S * n) {
+      for (int m = m1 + t0 * n; m < mt; m += S * n) {
         an = cadd(an, gn[(size_t)m * B + c]);
         if (!equator) as = cadd(as, gs[(size_t)m * B + c]);
       }
@@ -1269,7 +1274,7 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2)
       int mm = m2 + (t0 & 1) * n;
       if (mm >= 2 * n) mm -= 2 * n;
 #pragma unroll 4
-      for (int m = m2 + t0 * n; m < M; m += S * n) {
+      for (int m = m2 + t0 * n; m < mt; m += S * n) {
         an = cadd(an, gn[(size_t)m * B + c]);
         if (!equator) as = cadd(as, gs[(size_t)m * B + c]);
       }
@@ -1300,11 +1305,11 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2)
         return cmk<C>(cn.x - cs.y, -(cn.y + cs.x));
       };
       ring_dft_bs4<T, NT>(tb, p, Mbs, bs_nb, gc, buf, tq, n, b0 != bg0, input,
-                          fold_lanes(gc * min(bs_nb, 4) * (n >> 2), n, M, NT));
+                          fold_lanes(gc * min(bs_nb, 4) * (n >> 2), n, mt, NT));
     } else {
       // k = 0..n/2; each item also writes k' = n - k (conjugate sums)
       const int nk = gc * ((n >> 1) + 1);
-      const int S = fold_lanes(nk, n, M, NT);
+      const int S = fold_lanes(nk, n, mt, NT);
       const FastDiv dgc(gc);
       if (S > 1) {
         // short ring: S lanes per item (a wave-uniform loop: every lane of a

@@ -16,30 +16,27 @@
 
 namespace shtx {
 
-__global__ void k_ring_pairs(int N, int *rp_n, int *rp_sN, int *rp_sS, int *p0n, int *p0d, int *rp_M,
+__global__ void k_ring_pairs(int N, int *rp_n, int *rp_sN, int *rp_sS, int *p0n, int *rp_M,
                              int *rp_bsoff, double *z_out, double *sth_out, double *w_out) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= 2 * N) return;
   const int i = p + 1;  // north ring number, 1 .. 2N
   const long long npix = 12LL * N * N;
-  int n, sN, num, den;
+  int n, sN, num;
   double z;
   if (i < N) {  // north polar cap
     n = 4 * i;
     z = 1.0 - (double)((long long)i * i) / (3.0 * (double)N * (double)N);
     sN = 2 * i * (i - 1);
     num = 1;
-    den = 4 * i;
   } else {  // belt, north half (incl. equator)
     n = 4 * N;
     z = (double)(4 * N - 2 * i) / (3.0 * (double)N);
     sN = 2 * N * (N - 1) + 4 * N * (i - N);
     if (((i - N) & 1) == 0) {
       num = 1;
-      den = 4 * N;
     } else {
       num = 0;
-      den = 1;
     }
   }
   // south partner 4N - i: same length and phi0; RING start by symmetry
@@ -56,7 +53,6 @@ __global__ void k_ring_pairs(int N, int *rp_n, int *rp_sN, int *rp_sS, int *p0n,
   rp_sN[p] = sN;
   rp_sS[p] = sS;
   p0n[p] = num;
-  p0d[p] = den;
   z_out[p] = z;
   sth_out[p] = sqrt((1.0 - z) * (1.0 + z));
   w_out[p] = 4.0 * M_PI / (double)npix;
@@ -354,6 +350,23 @@ __global__ void k_ring2nest_table(int lgn, uint32_t *r2n) {
   r2n[start + (uint32_t)(j - 1)] = p;
 }
 
+// rp_mtop: above it every lambda_lm of the ring is negligible (no seed), so its
+// synthesis spectrum is zero there.  64 ring pairs and kTopRows orders at a time.
+constexpr int kTopRows = 16;
+__global__ void k_mtop(int L, int Rp, const int *seed_l, int *mtop) {
+  __shared__ int top[64];
+  const int p = blockIdx.x * 64 + threadIdx.x;
+  if (threadIdx.y == 0) top[threadIdx.x] = 0;
+  __syncthreads();
+  if (p < Rp) {
+    int m = L - (int)threadIdx.y;
+    while (m >= 0 && seed_l[(size_t)m * Rp + p] > L) m -= kTopRows;
+    atomicMax(&top[threadIdx.x], m + 1);
+  }
+  __syncthreads();
+  if (p < Rp && threadIdx.y == 0) mtop[p] = top[threadIdx.x];
+}
+
 hipError_t launch_tables_build(int nside, int lmax, void *base, hipStream_t st) {
   const TableOffsets o = table_offsets(nside, lmax);
   char *b = static_cast<char *>(base);
@@ -361,7 +374,7 @@ hipError_t launch_tables_build(int nside, int lmax, void *base, hipStream_t st) 
   auto I = [&](size_t off) { return reinterpret_cast<int *>(b + off); };
   auto D = [&](size_t off) { return reinterpret_cast<double *>(b + off); };
   hipLaunchKernelGGL(k_ring_pairs, dim3((Rp + 255) / 256), dim3(256), 0, st, nside, I(o.rp_n), I(o.rp_sN),
-                     I(o.rp_sS), I(o.rp_p0n), I(o.rp_p0d), I(o.rp_M), I(o.rp_bsoff), D(o.rp_z), D(o.rp_sth),
+                     I(o.rp_sS), I(o.rp_p0n), I(o.rp_M), I(o.rp_bsoff), D(o.rp_z), D(o.rp_sth),
                      D(o.rp_w));
   hipLaunchKernelGGL(k_coefs, dim3((lmax + 1 + 63) / 64), dim3(64), 0, st, lmax, D(o.coefA), D(o.coefC));
   {
@@ -373,6 +386,7 @@ hipError_t launch_tables_build(int nside, int lmax, void *base, hipStream_t st) 
   hipLaunchKernelGGL(k_lambda_mm, dim3((Rp + 63) / 64), dim3(64), 0, st, lmax, Rp, D(o.rp_sth), sv);
   hipLaunchKernelGGL(k_seeds, dim3((Rp + 63) / 64, lmax + 1), dim3(64), 0, st, lmax, Rp, D(o.rp_z),
                      D(o.coefA), I(o.seed_l), sv);
+  hipLaunchKernelGGL(k_mtop, dim3((Rp + 63) / 64), dim3(64, kTopRows), 0, st, lmax, Rp, I(o.seed_l), I(o.rp_mtop));
   hipLaunchKernelGGL(k_roots, dim3((4 * nside + 255) / 256, nside), dim3(256), 0, st, nside,
                      reinterpret_cast<double2 *>(b + o.roots64), reinterpret_cast<float2 *>(b + o.roots32));
   if (o.nitems > 0) {
