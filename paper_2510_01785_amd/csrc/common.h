@@ -150,10 +150,19 @@ __host__ __device__ inline ChanGroup chan_group(int b, int batch, int gmax) {
 // stored).
 constexpr size_t kCoefPadTable = kBlockL + 8;
 
+// Orders of a ring pair that any lambda of it reaches the seed threshold at, from
+// its rp_mtop word: m < ring_orders; and the most of its aligned chunk of
+// kOrderChunk ring pairs.  The Legendre analysis kernels leave out slices of ring
+// pairs (at most a chunk, aligned) with no active ring, so they read the spectra
+// of a pair for m < chunk_orders only.
+constexpr int kOrderChunk = 256;
+__host__ __device__ inline int ring_orders(uint32_t w) { return (int)(w & 0xffffu); }
+__host__ __device__ inline int chunk_orders(uint32_t w) { return (int)(w >> 16); }
+
 // Byte offsets of the pieces of the resident table buffer.
 struct TableOffsets {
   size_t rp_n, rp_sN, rp_sS, rp_p0n;          // int32 [Rp]
-  size_t rp_mtop;                             // int32 [Rp]: 1 + the largest m with a stored seed
+  size_t rp_mtop;                             // uint32 [Rp]: ring_orders, chunk_orders
   size_t rp_M, rp_bsoff;                      // int32 [Rp]: Bluestein length (0: mixed radix; kButterflyRing), offset
   size_t rp_z, rp_sth, rp_w;                  // double [Rp]
   size_t coefA, coefC;                        // double [nalm + kCoefPadTable], zero padding
@@ -226,7 +235,8 @@ inline TableOffsets table_offsets(int nside, int lmax) {
 
 struct Tables {
   int nside, lmax, npairs, npix, mmax_bs, nitems;
-  const int *rp_n, *rp_sN, *rp_sS, *rp_p0n, *rp_mtop, *rp_M, *rp_bsoff;
+  const int *rp_n, *rp_sN, *rp_sS, *rp_p0n, *rp_M, *rp_bsoff;
+  const uint32_t *rp_mtop;
   const double *rp_z, *rp_sth, *rp_w;
   const double *coefA, *coefC;
   const int *seed_l;
@@ -256,7 +266,7 @@ inline Tables tables_view(const void *base, int nside, int lmax) {
   t.rp_sN = reinterpret_cast<const int *>(b + o.rp_sN);
   t.rp_sS = reinterpret_cast<const int *>(b + o.rp_sS);
   t.rp_p0n = reinterpret_cast<const int *>(b + o.rp_p0n);
-  t.rp_mtop = reinterpret_cast<const int *>(b + o.rp_mtop);
+  t.rp_mtop = reinterpret_cast<const uint32_t *>(b + o.rp_mtop);
   t.rp_M = reinterpret_cast<const int *>(b + o.rp_M);
   t.rp_bsoff = reinterpret_cast<const int *>(b + o.rp_bsoff);
   t.rp_z = reinterpret_cast<const double *>(b + o.rp_z);

@@ -295,11 +295,11 @@ static int longest_xcd_items(int L) {
 // 512 per row written.
 __global__ void __launch_bounds__(256)
     k_pack_spectra_bf16(const uint32_t *__restrict__ XE, const uint32_t *__restrict__ XO, u32x4_t *__restrict__ XT,
-                        int B, int M, int Rp, int nrb, int ng) {
+                        int B, int M, int Rp, int nrb, int ng, const uint32_t *__restrict__ mtop) {
   const int col = threadIdx.x & 31;
   const int m = blockIdx.x * 8 + (threadIdx.x >> 5);
   const int rb = blockIdx.y, g = blockIdx.z % ng, par = blockIdx.z / ng;
-  if (m >= M) return;
+  if (m >= chunk_orders(mtop[8 * rb])) return;  // (at most M) not read, nor stored by the ring FFT
   const uint32_t *X = par ? XO : XE;
   const int c = 16 * g + (col >> 1), sh = 16 * (col & 1);
   uint32_t v[8];
@@ -324,7 +324,7 @@ hipError_t launch_pack_spectra_bf16(const Tables &tb, int B, const uint32_t *XE,
   const int M = tb.lmax + 1, Rp = tb.npairs, nrb = (Rp + 7) / 8, ng = (B + 15) / 16;
   if (2 * ng > 65535 || nrb > 65535) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_pack_spectra_bf16, dim3((M + 7) / 8, nrb, 2 * ng), dim3(256), 0, st, XE, XO,
-                     static_cast<u32x4_t *>(xt), B, M, Rp, nrb, ng);
+                     static_cast<u32x4_t *>(xt), B, M, Rp, nrb, ng, tb.rp_mtop);
   return hipGetLastError();
 }
 

@@ -413,7 +413,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NC == 1
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) wh = min(wh, __shfl_xor(wh, o));
   const int wl = __builtin_amdgcn_readfirstlane(wh);
-  if (wl > L && __all(!pok || m >= tb.rp_mtop[p])) return;  // zero spectra, which the ring FFT does not read
+  if (wl > L && __all(!pok || m >= ring_orders(tb.rp_mtop[p]))) return;  // zero spectra, which the ring FFT does not read
   f32x16 acc[NC][4];
 #pragma unroll
   for (int n = 0; n < NC; ++n)

@@ -303,7 +303,7 @@ __global__ void __launch_bounds__(64)
 #pragma unroll
   for (int t = 0; t < 4; ++t) wl_t[t] = __builtin_amdgcn_readfirstlane(__shfl(wh, 16 * t));
   const int wl = min(min(wl_t[0], wl_t[1]), min(wl_t[2], wl_t[3]));
-  if (wl > L && __all(!pok || m >= tb.rp_mtop[p])) return;  // zero spectra, which the ring FFT does not read
+  if (wl > L && __all(!pok || m >= ring_orders(tb.rp_mtop[p]))) return;  // zero spectra, which the ring FFT does not read
   f64x4_t acc[4][2][CT];  // [tile][parity][column tile]
 #pragma unroll
   for (int t = 0; t < 4; ++t)

@@ -345,7 +345,7 @@ __global__ void __launch_bounds__(64)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int p = chunk * 64 * R + 64 * r + j;
-      none &= p >= Rp || m >= tb.rp_mtop[p];
+      none &= p >= Rp || m >= ring_orders(tb.rp_mtop[p]);
     }
     if (__all(none)) return;  // zero spectra, which the ring FFT does not read
   }

@@ -350,13 +350,14 @@ __global__ void k_ring2nest_table(int lgn, uint32_t *r2n) {
   r2n[start + (uint32_t)(j - 1)] = p;
 }
 
-// rp_mtop: above it every lambda_lm of the ring is negligible (no seed), so its
-// synthesis spectrum is zero there.  64 ring pairs and kTopRows orders at a time.
-constexpr int kTopRows = 16;
-__global__ void k_mtop(int L, int Rp, const int *seed_l, int *mtop) {
-  __shared__ int top[64];
-  const int p = blockIdx.x * 64 + threadIdx.x;
+// rp_mtop: a workgroup per chunk of ring pairs, kTopRows orders at a time.
+constexpr int kTopRows = 4;
+__global__ void __launch_bounds__(kOrderChunk * kTopRows)
+    k_mtop(int L, int Rp, const int *seed_l, uint32_t *mtop) {
+  __shared__ int top[kOrderChunk], chunk;
+  const int p = blockIdx.x * kOrderChunk + threadIdx.x;
   if (threadIdx.y == 0) top[threadIdx.x] = 0;
+  if (threadIdx.x == 0 && threadIdx.y == 0) chunk = 0;
   __syncthreads();
   if (p < Rp) {
     int m = L - (int)threadIdx.y;
@@ -364,7 +365,9 @@ __global__ void k_mtop(int L, int Rp, const int *seed_l, int *mtop) {
     atomicMax(&top[threadIdx.x], m + 1);
   }
   __syncthreads();
-  if (p < Rp && threadIdx.y == 0) mtop[p] = top[threadIdx.x];
+  if (threadIdx.y == 0) atomicMax(&chunk, top[threadIdx.x]);
+  __syncthreads();
+  if (p < Rp && threadIdx.y == 0) mtop[p] = (uint32_t)top[threadIdx.x] | (uint32_t)chunk << 16;
 }
 
 hipError_t launch_tables_build(int nside, int lmax, void *base, hipStream_t st) {
@@ -386,7 +389,8 @@ hipError_t launch_tables_build(int nside, int lmax, void *base, hipStream_t st) 
   hipLaunchKernelGGL(k_lambda_mm, dim3((Rp + 63) / 64), dim3(64), 0, st, lmax, Rp, D(o.rp_sth), sv);
   hipLaunchKernelGGL(k_seeds, dim3((Rp + 63) / 64, lmax + 1), dim3(64), 0, st, lmax, Rp, D(o.rp_z),
                      D(o.coefA), I(o.seed_l), sv);
-  hipLaunchKernelGGL(k_mtop, dim3((Rp + 63) / 64), dim3(64, kTopRows), 0, st, lmax, Rp, I(o.seed_l), I(o.rp_mtop));
+  hipLaunchKernelGGL(k_mtop, dim3((Rp + kOrderChunk - 1) / kOrderChunk), dim3(kOrderChunk, kTopRows), 0, st, lmax, Rp,
+                     I(o.seed_l), reinterpret_cast<uint32_t *>(b + o.rp_mtop));
   hipLaunchKernelGGL(k_roots, dim3((4 * nside + 255) / 256, nside), dim3(256), 0, st, nside,
                      reinterpret_cast<double2 *>(b + o.roots64), reinterpret_cast<float2 *>(b + o.roots32));
   if (o.nitems > 0) {
