@@ -69,25 +69,23 @@ def parse():
 
 
 # Legendre kernels: the library takes the matrix-core kernels for FP32 /
-# BF16 contraction and for FP64 from this many channels up (its default
+# BF16 contraction and for FP64 from these channel counts (its default
 # switch points), the vector-ALU kernels otherwise
-MFMA_MIN_BATCH = {"fwd": 5, "inv": 8}
-MFMA64_MIN_BATCH = {"fwd": 3, "inv": 5}
-
-
-def on_mfma(stage, dtype, batch):
-    d = stage.split("_")[1]
+def on_mfma(stage, dtype, batch, nside):
+    fwd = stage == "legendre_fwd"
     if dtype == "f64":
-        return batch >= MFMA64_MIN_BATCH[d]
-    return dtype in ("f32", "bf16") and batch >= MFMA_MIN_BATCH[d]
+        return batch >= (5 if not fwd else 3 if nside <= 256 else 4) or (not fwd and batch == 3 and nside <= 128)
+    if bf16_mfma(stage, dtype, batch):
+        return True
+    return batch >= (5 if fwd or nside > 256 else 3) or (batch == 3 and nside <= 256)
 
 
 def bf16_mfma(stage, dtype, batch):
-    """BF16 maps take the BF16 matrix-core analysis from the FP32 switch point."""
-    return stage == "legendre_fwd" and dtype == "bf16" and batch >= MFMA_MIN_BATCH["fwd"]
+    """BF16 maps take the BF16 matrix-core analysis from 5 channels."""
+    return stage == "legendre_fwd" and dtype == "bf16" and batch >= 5
 
 
-def stage_kernel(stage, dtype, batch):
+def stage_kernel(stage, dtype, batch, nside):
     """(kernel symbol, source file) that runs `stage`."""
     if bf16_mfma(stage, dtype, batch):
         return ("k_legendre_fwd_bf16", "legendre_bf16.hip")
@@ -95,7 +93,7 @@ def stage_kernel(stage, dtype, batch):
         return ("k_pack_spectra_bf16", "legendre_bf16.hip")
     if stage.startswith("legendre"):
         d = stage.split("_")[1]
-        if not on_mfma(stage, dtype, batch):
+        if not on_mfma(stage, dtype, batch, nside):
             return ("k_legendre_%s_valu" % d, "legendre_valu.hip")
         return ("k_legendre_%s_mfma64" % d, "legendre_mfma64.hip") if dtype == "f64" else \
             ("k_legendre_%s_mfma" % d, "legendre_mfma.hip")
@@ -174,8 +172,8 @@ def oracle_check(nside, lmax, f0, a0_gpu, g0_gpu):
 def stage_peak(bound, dtype):
     """Peak (flop/s or B/s) of a stage's bound: the matrix cores of the
     contraction's precision (FP32, or FP64 at the FP64 rate; BF16 maps on
-    the FP32 contraction count as FP32), the vector ALUs of the compute
-    precision otherwise."""
+    the FP32 contraction count as FP32, whose kernels form the products from
+    BF16 parts), the vector ALUs of the compute precision otherwise."""
     if bound == "hbm":
         return PEAK["hbm_GBs"] * 1e9
     if bound == "mfma":
@@ -788,12 +786,12 @@ def main():
     npix = 12 * nside * nside
     spec_bytes = 2 * (lmax + 1) * 2 * nside * B * csize
     alm_bytes = (lmax + 1) * (lmax + 2) // 2 * B * csize
-    mfma = dom.startswith("legendre") and on_mfma(dom, args.dtype, B)
+    mfma = dom.startswith("legendre") and on_mfma(dom, args.dtype, B, nside)
     # Legendre work: 4 flops (complex += real * complex) per executed (l, m,
     # ring pair) triple and channel; the executed triangle skips the l where
     # lambda_lm(z_p) is negligible (the full triangle is reported beside it)
-    bf_ = "mfma" if on_mfma("legendre_fwd", args.dtype, B) else "alu"
-    bi_ = "mfma" if on_mfma("legendre_inv", args.dtype, B) else "alu"
+    bf_ = "mfma" if on_mfma("legendre_fwd", args.dtype, B, nside) else "alu"
+    bi_ = "mfma" if on_mfma("legendre_inv", args.dtype, B, nside) else "alu"
     # BF16 spectra: 4 bytes per complex value
     spec_fwd = spec_bytes // 2 if bf16_mfma("legendre_fwd", args.dtype, B) else spec_bytes
     work = {
@@ -821,7 +819,7 @@ def main():
     sec = stages[dom]["ms_per_call"] / 1000.0
     achieved = amount / sec / (1e12 if unit == "TFLOP/s" else 1e9)
     workload = "nside%d_lmax%d_b%d_%s" % (nside, lmax, B, args.dtype)
-    kname, kfile = stage_kernel(dom, args.dtype, B)
+    kname, kfile = stage_kernel(dom, args.dtype, B, nside)
     traffic = measured_traffic(kname, kfile, workload) if (mfma or unit != "TFLOP/s" or
                                                           bf16_mfma(dom, args.dtype, B)) else None
     roof = dict(kernel=kname, bound=bound, achieved=round(achieved, 3), peak=peak, unit=unit,

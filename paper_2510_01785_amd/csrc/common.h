@@ -49,7 +49,8 @@ __host__ __device__ inline size_t roots_offset(int i) {
 
 // Ring lengths n = 4i whose odd part has a prime factor above this are
 // transformed with Bluestein's chirp-z algorithm (Eq. (17)-(23)) on a
-// power-of-two length; the others with mixed radix 4/2/3/5/7/11/13.
+// power-of-two length (except where the register butterflies take them, below);
+// the others with mixed-radix stages.
 constexpr int kMaxDirectPrime = 13;
 // Prime factors that the ring FFT's register butterflies take (ring_fft.hip); ring
 // pairs within them that also have a chirp carry kButterflyRing in rp_M.
