@@ -91,6 +91,35 @@ __device__ __forceinline__ void mfma_split2(const u32x4 (&a0)[3], const u32x4 (&
   }
 }
 
+// Range.  A part below 2^-133, the smallest BF16 value, is lost, so an operand of
+// less than 2^-109 would not keep its 24 bits, and one that rounds to 2^128 would
+// have an infinite part.  So the synthesis' slab holds halves of the coefficients, and
+// both kernels multiply a column of the channels' operands, and with it its
+// sums, by kTinyScale until the first value of kTinyBelow or more arrives.  From then
+// on values below 2^-109 lose what is under 2^-134, 2^94 times smaller than that value
+// (lambda is taken as zero below 2^-64).  The scaled operands are below 2^24 and, where
+// not zero, at least 2^-86.  In ordinary data the first operands of a wave take all its
+// columns past kTinyBelow; a wave with a column that stays below it (tiny values, a zero
+// channel) takes 3% longer (Nside 1024 L 2047 B 16, calls: analysis 2.91 -> 3.00 ms,
+// synthesis 2.68 -> 2.77).
+constexpr float kTinyBelow = 0x1p-40f;
+constexpr float kTinyScale = 0x1p64f, kTinyUndo = 0x1p-64f;
+// The scale of a lane's column (kTinyScale or 1) after the operands x(0) .. x(n - 1) of
+// this lane, and what its sums so far have to be multiplied by.  Four of the operands
+// show it in ordinary data.
+template <int n, typename F> __device__ __forceinline__ float tiny_step(F x, float &scale) {
+  float big = fmaxf(fmaxf(fabsf(x(0)), fabsf(x(n / 4))), fmaxf(fabsf(x(n / 2)), fabsf(x(3 * n / 4))));
+  if (!__all(scale == 1.f || big >= kTinyBelow)) {
+#pragma unroll
+    for (int i = 0; i < n; ++i) big = fmaxf(big, fabsf(x(i)));
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(big), __float_as_uint(big), false, false);
+    big = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));  // of both lanes of the column
+  }
+  const float undo = scale != 1.f && big >= kTinyBelow ? kTinyUndo : 1.f;
+  scale *= undo;
+  return undo;
+}
+
 // Word 3 of a raw buffer resource on gfx9-family GPUs (untyped 32-bit
 // loads, no swizzle).
 constexpr int kBufferWord3 = 0x00020000;
@@ -151,6 +180,9 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2,
   for (int a = 0; a < 4; ++a)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[a][r] = 0.f;
+  // the scale of this lane's column (the imaginary ones of m = 0 are not used)
+  float scale = m == 0 && (col & 1) ? 1.f : kTinyScale;
+  int tiny = 2;  // uniform: 0 no column of the wave is scaled, 1 some are, 2 and nothing is summed yet
 
   // this lane's ring per chunk: recurrence start (kBlockL: not
   // active in this block), checkpoint and z, fetched one chunk ahead
@@ -301,6 +333,23 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2,
     // every l of the second is beyond lmax (output rows that are never stored)
     const bool first = tfirst < kSubL;
     if (first) recurrence(0);
+    if (tiny) {
+      const float undo = tiny_step<64>([&](int i) { return xf[i & 1][i >> 1]; }, scale);
+      if (tiny == 1 && __any(undo != 1.f)) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[a][r] *= undo;
+      }
+      tiny = __any(scale != 1.f) ? 1 : 0;
+      if (tiny) {
+#pragma unroll
+        for (int s = 0; s < 32; ++s) {
+          xf[0][s] *= scale;
+          xf[1][s] *= scale;
+        }
+      }
+    }
 #pragma unroll
     for (int par = 0; par < 2; ++par)
 #pragma unroll
@@ -320,6 +369,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2,
   // layout alm[b][idx(l, m)] = f_m c_lm a (Im = 0 for m = 0), or add to it
   __syncthreads();
   float *red = tile;
+  const float unscale = scale != 1.f ? kTinyUndo : 1.f;
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
     const int hb = a >> 1, par = a & 1;
@@ -327,7 +377,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2,
     for (int r = 0; r < 16; ++r) {
       const int i = 8 * (r >> 2) + 4 * h + (r & 3);
       const int lrel = hb * kSubL + 2 * i + par;
-      red[(w * kBlockL + lrel) * kRedRS + col] = acc[a][r];
+      red[(w * kBlockL + lrel) * kRedRS + col] = unscale * acc[a][r];
     }
   }
   __syncthreads();
@@ -372,8 +422,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2,
 // consecutive XCDs): they share the a_m slabs in L2.  A wave writes, per ring
 // pair, whole [m][batch] rows of the synthesis spectra (32 consecutive floats
 // per ring: one 128-byte line at 16 channels).  The slab holds half of each
-// coefficient (so that no finite one rounds up to a BF16 infinity); the sums
-// are doubled as they are stored.
+// coefficient; the sums are doubled as they are stored.
 //
 // Bound by the vector ALU: per group of 32 l some 400 vector instructions
 // (recurrence 72, conversions 32, splitting of lambda 176 and of the rows 88,
@@ -443,13 +492,18 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NC == 1
     const int c = min(b0 + 16 * n + (col >> 1), B - 1);
     vo[n] = 16u * h * rowb + 8u * c + 4u * (col & 1);
   }
+  float scale[NC];   // of this lane's columns (the imaginary ones of m = 0 are zero)
+  bool tiny = true;  // some column of the wave is scaled (uniform)
+#pragma unroll
+  for (int n = 0; n < NC; ++n) scale[n] = m == 0 && (col & 1) ? 1.f : kTinyScale;
   double prv = 0.0, cur = 0.0;
   // One group of 32 steps from l = lq; ac holds A_l of its first 8 steps and
   // receives those of the next group's.  TAIL: the group holds l > lmax, whose
   // coefficients are taken as zero (the recurrence stays finite there and
-  // meets zero rows of B).
-  auto group = [&](int lq, double (&ac)[8], auto tail) {
-    constexpr bool TAIL = decltype(tail)::value;
+  // meets zero rows of B).  CHECK: columns may be scaled (a test of `tiny` in the
+  // loop without it took 2.5% more).
+  auto group = [&](int lq, double (&ac)[8], auto tail, auto check) {
+    constexpr bool TAIL = decltype(tail)::value, CHECK = decltype(check)::value;
     float bf[NC][2][8];
 #pragma unroll
     for (int e = 0; e < 8; ++e)
@@ -498,6 +552,30 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NC == 1
 #pragma unroll
       for (int u = 0; u < 8; ++u) ac[u] = an[u];
     }
+    if (CHECK && tiny) {
+      bool any = false;
+#pragma unroll
+      for (int n = 0; n < NC; ++n) {
+        const float undo = tiny_step<16>([&](int i) { return bf[n][i & 1][i >> 1]; }, scale[n]);
+        if (lq != wl && __any(undo != 1.f)) {
+#pragma unroll
+          for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[n][a][r] *= undo;
+        }
+        any |= scale[n] != 1.f;
+      }
+      tiny = __any(any);
+      if (tiny) {
+#pragma unroll
+        for (int n = 0; n < NC; ++n)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            bf[n][0][e] *= scale[n];
+            bf[n][1][e] *= scale[n];
+          }
+      }
+    }
 #pragma unroll
     for (int par = 0; par < 2; ++par) {
       __builtin_amdgcn_sched_barrier(0);
@@ -525,8 +603,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NC == 1
     for (int u = 0; u < 8; ++u) ac[u] = Ag[wl + u];
     int lq = wl;
 #pragma unroll 1
-    for (; lq + 31 <= L; lq += 32) group(lq, ac, std::false_type{});
-    if (lq <= L) group(lq, ac, std::true_type{});
+    for (; tiny && lq + 31 <= L; lq += 32) group(lq, ac, std::false_type{}, std::true_type{});
+#pragma unroll 1
+    for (; lq + 31 <= L; lq += 32) group(lq, ac, std::false_type{}, std::false_type{});
+    if (lq <= L) group(lq, ac, std::true_type{}, std::true_type{});
   }
   float *gn = reinterpret_cast<float *>(GN);
   float *gs = reinterpret_cast<float *>(GS);
@@ -536,6 +616,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NC == 1
     const int c = b0 + 16 * n + (col >> 1);
     if (c >= B) continue;
     const size_t cofs = lay.idx(0, c, m) * 2 + (col & 1);
+    const float out = scale[n] != 1.f ? 2.f * kTinyUndo : 2.f;  // (the coefficients came halved)
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
 #pragma unroll
@@ -544,8 +625,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NC == 1
         const int pr = chunk * kInvRings + hh * 32 + i;
         if (pr >= Rp) continue;
         const size_t o = (size_t)pr * ringf + cofs;
-        gn[o] = 2.f * (acc[n][2 * hh][r] + acc[n][2 * hh + 1][r]);
-        gs[o] = 2.f * (acc[n][2 * hh][r] - acc[n][2 * hh + 1][r]);
+        gn[o] = out * (acc[n][2 * hh][r] + acc[n][2 * hh + 1][r]);
+        gs[o] = out * (acc[n][2 * hh][r] - acc[n][2 * hh + 1][r]);
       }
     }
   }
