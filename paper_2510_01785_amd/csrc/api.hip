@@ -243,22 +243,23 @@ bool force_valu() {
   return e && e[0] == '1';
 }
 
-// Legendre step of the analysis; both kernels write the caller's layout
-// themselves (factors f0 / fm, optional accumulation).
-template <typename T> hipError_t legendre_fwd(const Tables &tb, int B, const cplx<T> *XE, const cplx<T> *XO,
-                                              cplx<T> *alm, double f0, double fm, int accum, hipStream_t st) {
-  return launch_legendre_fwd_valu<T>(tb, B, XE, XO, alm, f0, fm, accum, st);
+// Legendre kernel of an analysis: matrix cores (enough channels) or vector ALUs.
+template <typename T> bool fwd_on_matrix_cores(const Tables &tb, int B) {
+  if (!mfma_fwd_supported(tb) || force_valu()) return false;
+  return sizeof(T) == 4 ? fwd_on_mfma(B, tb.nside) : B >= mfma64_min_batch(false, tb.nside);
 }
-template <> hipError_t legendre_fwd<double>(const Tables &tb, int B, const double2 *XE, const double2 *XO,
-                                            double2 *alm, double f0, double fm, int accum, hipStream_t st) {
-  if (B >= mfma64_min_batch(false, tb.nside) && mfma_fwd_supported(tb) && !force_valu())
-    return launch_legendre_fwd_mfma64(tb, B, XE, XO, alm, f0, fm, accum, st);
+
+// Legendre step of the analysis; all kernels write the caller's layout
+// themselves (factors f0 / fm, optional accumulation).
+hipError_t legendre_fwd(const Tables &tb, int B, const double2 *XE, const double2 *XO, double2 *alm, double f0,
+                        double fm, int accum, bool mfma, hipStream_t st) {
+  if (mfma) return launch_legendre_fwd_mfma64(tb, B, XE, XO, alm, f0, fm, accum, st);
   return launch_legendre_fwd_valu<double>(tb, B, XE, XO, alm, f0, fm, accum, st);
 }
-template <> hipError_t legendre_fwd<float>(const Tables &tb, int B, const float2 *XE, const float2 *XO, float2 *alm,
-                                           double f0, double fm, int accum, hipStream_t st) {
-  if (fwd_on_mfma(B, tb.nside) && mfma_fwd_supported(tb) && !force_valu())
-    return launch_legendre_fwd_mfma(tb, B, XE, XO, alm, f0, fm, accum, st);
+// (the FP32 matrix-core kernel takes halves of the spectra)
+hipError_t legendre_fwd(const Tables &tb, int B, const float2 *XE, const float2 *XO, float2 *alm, double f0,
+                        double fm, int accum, bool mfma, hipStream_t st) {
+  if (mfma) return launch_legendre_fwd_mfma(tb, B, XE, XO, alm, 2.0 * f0, 2.0 * fm, accum, st);
   return launch_legendre_fwd_valu<float>(tb, B, XE, XO, alm, f0, fm, accum, st);
 }
 // Synthesis Legendre kernel of a call: matrix cores (enough channels) or
@@ -326,13 +327,15 @@ int run_analysis(const Tables &tb, int B, const TIn *map, cplx<T> *alm, const do
       return status_of(launch_legendre_fwd_bf16(tb, B, w.almt, alm, f0, fm, accumulate, st, lam));
     }
   }
+  const bool mfma = fwd_on_matrix_cores<T>(tb, B);  // read once: both kernels follow the same choice
+  const double half = mfma && sizeof(T) == 4 ? 0.5 : 1.0;
   {
     StageTimer t(kStFftFwd, st);
-    e = launch_ring_fft_fwd<TIn, T, cplx<T>>(tb, B, map, wtab, wscale, pixw, w.specA, w.specB, st, nested);
+    e = launch_ring_fft_fwd<TIn, T, cplx<T>>(tb, B, map, wtab, half * wscale, pixw, w.specA, w.specB, st, nested);
   }
   if (e != hipSuccess) return SHTX_ERR_HIP;
   StageTimer t(kStLegFwd, st);
-  return status_of(legendre_fwd<T>(tb, B, w.specA, w.specB, alm, f0, fm, accumulate, st));
+  return status_of(legendre_fwd(tb, B, w.specA, w.specB, alm, f0, fm, accumulate, mfma, st));
 }
 
 // synthesis chain: caller layout with factors -> Legendre -> ring FFT

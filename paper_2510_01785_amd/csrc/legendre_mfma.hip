@@ -93,8 +93,8 @@ __device__ __forceinline__ void mfma_split2(const u32x4 (&a0)[3], const u32x4 (&
 
 // Range.  A part below 2^-133, the smallest BF16 value, is lost, so an operand of
 // less than 2^-109 would not keep its 24 bits, and one that rounds to 2^128 would
-// have an infinite part.  So the synthesis' slab holds halves of the coefficients, and
-// both kernels multiply a column of the channels' operands, and with it its
+// have an infinite part.  So the callers hand over halves of the channels' operands
+// (spectra, coefficients), and the kernels multiply a column of them, and with it its
 // sums, by kTinyScale until the first value of kTinyBelow or more arrives.  From then
 // on values below 2^-109 lose what is under 2^-134, 2^94 times smaller than that value
 // (lambda is taken as zero below 2^-64).  The scaled operands are below 2^24 and, where

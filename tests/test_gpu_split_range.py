@@ -82,3 +82,20 @@ def test_magnitude_changes(shtx, first, then):
         big = 2.0 ** max(first, then)
         assert rel_l2(got / big, ref / big) <= TOL
 
+
+def test_largest_spectra(shtx):
+    """A ring spectrum just below the largest FP32 value (ring weight 2), whose BF16
+    rounding is infinite, in the last channel."""
+    nside, lmax, batch = 16, 20, 5
+    print("\n[case] spectra below 2^128", flush=True)
+    r = 10  # ring number, 4 r pixels from pixel 2 r (r - 1) on
+    x = np.zeros((batch, 12 * nside * nside), dtype=np.float32)
+    x[:, 2 * r * (r - 1):2 * r * (r + 1)] = 1.0
+    x[-1] *= np.float32(2.0 ** 127 * (1 - 2.0 ** -11) / (4 * r))
+    w = np.full(2 * nside, 2.0)
+    got = shtx.map2alm_weighted_raw(torch.tensor(x, device="cuda"), lmax, torch.tensor(w)).cpu().numpy()
+    # (the oracle's ring weights are one per ring, mirrored here)
+    ref = sht.map2alm(x.astype(np.float64), lmax, nside, ring_weights=np.full(4 * nside - 1, 2.0))
+    assert np.isfinite(got).all()
+    big = np.abs(ref).max(axis=1, keepdims=True)
+    assert rel_l2(got.astype(np.complex128) / big, ref / big) <= TOL
