@@ -437,6 +437,9 @@ __global__ void __launch_bounds__(64)
   }
 }
 
+// A row of the grid per channel group, as many rows as a launch may have.
+constexpr int kMaxGridRows = 65535;
+
 template <typename T, int BG, int R, int RI, int NW>
 static void launch_fwd_cfg(const Tables &tb, int B, int b0, int ngroups, const cplx<T> *XE, const cplx<T> *XO,
                            cplx<T> *alm, double f0, double fm, int accum, hipStream_t st) {
@@ -446,8 +449,9 @@ static void launch_fwd_cfg(const Tables &tb, int B, int b0, int ngroups, const c
     for (int m = x; m <= tb.lmax; m += 8) c += (tb.lmax - m + kBlockL) / kBlockL;
     longest = std::max(longest, c);
   }
-  hipLaunchKernelGGL((k_legendre_fwd_valu<T, BG, R, RI, NW>), dim3(8 * longest, ngroups), dim3(64 * NW), 0, st, tb, B, b0, XE,
-                     XO, alm, (T)f0, (T)fm, accum);
+  for (int g = 0; g < ngroups; g += kMaxGridRows)
+    hipLaunchKernelGGL((k_legendre_fwd_valu<T, BG, R, RI, NW>), dim3(8 * longest, std::min(ngroups - g, kMaxGridRows)),
+                       dim3(64 * NW), 0, st, tb, B, b0 + BG * g, XE, XO, alm, (T)f0, (T)fm, accum);
 }
 
 // Rings per lane (in slices whose rings all start at the block, RI in the
@@ -498,8 +502,9 @@ static void launch_inv_cfg(const Tables &tb, int B, int b0, int ngroups, const c
                            cplx<T> *GN, cplx<T> *GS, hipStream_t st) {
   const int nch = (tb.npairs + 64 * R - 1) / (64 * R);
   const int nm = (tb.lmax + 1 + 7) / 8;
-  hipLaunchKernelGGL((k_legendre_inv_valu<T, BG, R>), dim3(8 * nm * nch, ngroups), dim3(64), 0, st, tb, B, b0,
-                     ALMT, lay, GN, GS);
+  for (int g = 0; g < ngroups; g += kMaxGridRows)
+    hipLaunchKernelGGL((k_legendre_inv_valu<T, BG, R>), dim3(8 * nm * nch, std::min(ngroups - g, kMaxGridRows)), dim3(64),
+                       0, st, tb, B, b0 + BG * g, ALMT, lay, GN, GS);
 }
 
 // Ring pairs per lane by the waves there are with one: more per lane share the
