@@ -45,6 +45,13 @@
  * Concurrent calls on different streams need distinct workspaces; a table
  * buffer may be shared by any number of concurrent calls once built.
  *
+ * Non-finite values stay in their channel.  There an infinite or NaN pixel
+ * makes the coefficients that its ring contributes to non-finite, and an
+ * infinite or NaN coefficient a_lm the pixels of every ring where lambda_lm
+ * counts; which of them are infinite and which NaN is not specified.  Rings
+ * where no lambda_l'm of its order m, l' <= lmax, reaches some 2^-64 take none of
+ * that order, so such a coefficient leaves their pixels finite.
+ *
  * Errors: arguments are checked before anything is launched; a failed check
  * returns a status code and launches nothing.  A launch failure returns
  * SHTX_ERR_HIP; a fault inside a kernel surfaces at the caller's next
