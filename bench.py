@@ -169,16 +169,22 @@ def oracle_check(nside, lmax, f0, a0_gpu, g0_gpu):
     return acc, cpu
 
 
-def stage_peak(bound, dtype):
-    """Peak (flop/s or B/s) of a stage's bound: the matrix cores of the
-    contraction's precision (FP32, or FP64 at the FP64 rate; BF16 maps on
-    the FP32 contraction count as FP32, whose kernels form the products from
-    BF16 parts), the vector ALUs of the compute precision otherwise."""
-    if bound == "hbm":
-        return PEAK["hbm_GBs"] * 1e9
-    if bound == "mfma":
-        return (PEAK["fp64_mfma_TFs"] if dtype == "f64" else PEAK["fp32_mfma_TFs"]) * 1e12
-    return (PEAK["fp64_vector_TFs"] if dtype == "f64" else PEAK["fp32_vector_TFs"]) * 1e12
+def legendre_work(stage, dtype, batch, nside, executed):
+    """(bound, amount, unit, peak) of a Legendre stage: 4 flops (complex += real *
+    complex) per executed (l, m, ring pair) triple and channel, at the peak of the unit
+    that runs them.  The FP32 matrix-core kernels form each product from six BF16
+    partial products, the BF16 analysis takes one; both are fed by the FP64 recurrence
+    (a multiply and a fused multiply-add, 3 flops, per triple, shared by the channels)
+    on the vector ALUs, which bounds them instead where it takes longer."""
+    flops = 4.0 * executed * batch
+    if not on_mfma(stage, dtype, batch, nside):
+        return "alu", flops, "TFLOP/s", PEAK["fp64_vector_TFs"] if dtype == "f64" else PEAK["fp32_vector_TFs"]
+    if dtype == "f64":
+        return "mfma", flops, "TFLOP/s", PEAK["fp64_mfma_TFs"]
+    peak = PEAK["bf16_mfma_TFs"] / (1 if bf16_mfma(stage, dtype, batch) else 6)
+    if 3.0 * executed / PEAK["fp64_vector_TFs"] >= flops / peak:
+        return "alu", 3.0 * executed, "TFLOP/s", PEAK["fp64_vector_TFs"]
+    return "mfma", flops, "TFLOP/s", peak
 
 
 def step_roofline(stages, work, dtype, B, ms_per_step):
@@ -787,17 +793,14 @@ def main():
     spec_bytes = 2 * (lmax + 1) * 2 * nside * B * csize
     alm_bytes = (lmax + 1) * (lmax + 2) // 2 * B * csize
     mfma = dom.startswith("legendre") and on_mfma(dom, args.dtype, B, nside)
-    # Legendre work: 4 flops (complex += real * complex) per executed (l, m,
-    # ring pair) triple and channel; the executed triangle skips the l where
-    # lambda_lm(z_p) is negligible (the full triangle is reported beside it)
-    bf_ = "mfma" if on_mfma("legendre_fwd", args.dtype, B, nside) else "alu"
-    bi_ = "mfma" if on_mfma("legendre_inv", args.dtype, B, nside) else "alu"
     # BF16 spectra: 4 bytes per complex value
     spec_fwd = spec_bytes // 2 if bf16_mfma("legendre_fwd", args.dtype, B) else spec_bytes
     work = {
-        # algorithmic work per call of each stage: (bound, amount, unit, peak)
-        "legendre_fwd": (bf_, 4.0 * executed * B, "TFLOP/s", stage_peak(bf_, args.dtype) / 1e12),
-        "legendre_inv": (bi_, 4.0 * executed * B, "TFLOP/s", stage_peak(bi_, args.dtype) / 1e12),
+        # algorithmic work per call of each stage: (bound, amount, unit, peak); the
+        # executed triangle of the Legendre stages skips the l where lambda_lm(z_p) is
+        # negligible (the full triangle is reported beside it)
+        "legendre_fwd": legendre_work("legendre_fwd", args.dtype, B, nside, executed),
+        "legendre_inv": legendre_work("legendre_inv", args.dtype, B, nside, executed),
         "ring_fft_fwd": ("hbm", float(npix * B * esize + spec_fwd), "GB/s", PEAK["hbm_GBs"]),
         "ring_fft_inv": ("hbm", float(npix * B * esize + spec_bytes), "GB/s", PEAK["hbm_GBs"]),
         "alm_in": ("hbm", 2.0 * alm_bytes, "GB/s", PEAK["hbm_GBs"]),
@@ -806,15 +809,6 @@ def main():
         "pack_bf16": ("hbm", float(spec_fwd + 2 * ((B + 15) // 16) * (lmax + 1) * ((2 * nside + 7) // 8) * 512),
                       "GB/s", PEAK["hbm_GBs"]),
     }
-    if bf16_mfma("legendre_fwd", args.dtype, B):
-        # BF16 matrix-core analysis: the BF16 contraction (4 T_exec B flops)
-        # takes 4 T_exec B / 2.5 PFLOP/s, below the FP64 recurrence it is fed
-        # by (a multiply and a fused multiply-add, 3 flops, per executed
-        # triple, shared by the channels) at the FP64 vector peak: that binds
-        t_mfma = 4.0 * executed * B / (PEAK["bf16_mfma_TFs"] * 1e12)
-        t_rec = 3.0 * executed / (PEAK["fp64_vector_TFs"] * 1e12)
-        work["legendre_fwd"] = (("alu", 3.0 * executed, "TFLOP/s", PEAK["fp64_vector_TFs"]) if t_rec >= t_mfma else
-                                ("mfma", 4.0 * executed * B, "TFLOP/s", PEAK["bf16_mfma_TFs"]))
     bound, amount, unit, peak = work[dom]
     sec = stages[dom]["ms_per_call"] / 1000.0
     achieved = amount / sec / (1e12 if unit == "TFLOP/s" else 1e9)
@@ -822,7 +816,7 @@ def main():
     kname, kfile = stage_kernel(dom, args.dtype, B, nside)
     traffic = measured_traffic(kname, kfile, workload) if (mfma or unit != "TFLOP/s" or
                                                           bf16_mfma(dom, args.dtype, B)) else None
-    roof = dict(kernel=kname, bound=bound, achieved=round(achieved, 3), peak=peak, unit=unit,
+    roof = dict(kernel=kname, bound=bound, achieved=round(achieved, 3), peak=round(peak, 1), unit=unit,
                 frac=round(achieved / peak, 4), traffic=traffic,
                 algorithmic=amount, per="launch" if B <= 16 else "call")
     if unit == "TFLOP/s":
