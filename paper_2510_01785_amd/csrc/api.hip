@@ -288,8 +288,9 @@ template <> hipError_t legendre_inv<float>(const Tables &tb, int B, const float2
 }
 
 // BF16 maps take the BF16 matrix-core contraction (BF16 spectra and
-// Legendre operands, FP32 accumulation) where the FP32 analysis would take
-// the matrix cores; SHTX_BF16_CONTRACT=f32 in the environment (read per
+// Legendre operands, FP32 accumulation) from 5 channels, and the FP32
+// contraction of their sizes below (fwd_on_mfma: on the matrix cores at 3
+// channels up to Nside 256); SHTX_BF16_CONTRACT=f32 in the environment (read per
 // call) keeps them on the FP32 contraction.
 template <typename TIn> bool bf16_contraction(const Tables &tb, int B) {
   if constexpr (!std::is_same<TIn, bf16_t>::value) {

@@ -22,16 +22,17 @@ namespace shtx {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 // FP32 products on the BF16 matrix cores.  An FP32 value is the sum of three
 // BF16 values, x = h + m + l with each part the rounding of what the ones
-// before it leave (8 bits each, 24 in all; exact down to the subnormal range
-// of l), and a product of two such values is taken as the six partial products
-// hh + hm + mh + hl + lh + mm; the three left out are below 2^-26 of it.  All
-// of them are exact in FP32 and are added in FP32 by the matrix core, 16 terms
-// of K to a rounding (the FP32 instruction: 2), so the sums are no further
-// from the exact ones than FP32 products' (random operands, relative l2
-// against FP64: 6.8e-7 for FP32 products, K 2048: 8.4e-7).  Six
-// v_mfma_f32_32x32x16_bf16 take 192 cycles for what eight
-// v_mfma_f32_32x32x2_f32 take 512, and the vector ALU issues beside them
-// (beside FP32 matrix instructions it does not: both use its multipliers).
+// before it leave (8 bits each, 24 in all: exact where l does not fall below
+// the BF16 range, see below), and a product of two such values is taken as the six
+// partial products hh + hm + mh + hl + lh + mm.  The three left out are at most
+// 2^-24 of it, one FP32 rounding (2^-27.5 in the root mean square of random
+// factors); leaving out any other adds 2.5e-6 and more to the sums' relative l2
+// error.  All partial products are exact in FP32 and are added in FP32 by the
+// matrix core, 16 terms of K to a rounding (the FP32 instruction: 2): random
+// operands, K 2048, relative l2 of the sums against FP64, 6.8e-7 with the parts,
+// 8.4e-7 with the FP32 instruction.  Six v_mfma_f32_32x32x16_bf16 take 192 cycles
+// for what eight v_mfma_f32_32x32x2_f32 take 512, and the vector ALU issues beside
+// them (beside FP32 matrix instructions it does not: both use its multipliers).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f32x16 mfma_bf(u32x4 a, u32x4 b, f32x16 c) {

@@ -552,9 +552,12 @@ __device__ __forceinline__ void fft_mixed(cplx<T> *buf, int n, int G, int pad, c
 }
 
 // The stages of analyses with BF16 spectra, lengths 4i with odd factors up to
-// kMaxDirectPrime: a value that the butterflies' other rounding takes across a BF16
-// boundary moves by 2^-8 (Nside 128 .. 1024, some hundred calls: up to 5e-3 of the
-// coefficients' scale), so these spectra keep the sums they have.
+// kMaxDirectPrime.  They are no more exact than the butterflies (relative l2 against
+// the FP64 oracle, sums / butterflies: Nside 128 L 301 B 5 2.338e-3 / 2.338e-3, Nside
+// 1024 L 1100 B 5 2.353e-3 / 2.353e-3) and slower (Nside 1024 B 16 0.99 ms, FP32 spectra
+// 0.90), but another rounding takes single values across a BF16 boundary, 2^-8 of
+// them: with these sums the coefficients of BF16 maps stay bit for bit what they were
+// (with the butterflies, up to 5e-3 of their scale off).
 // Radix-4/2 stage (span p):
 template <typename T, int NT, int R>
 __device__ __forceinline__ void stage_mix_p2(cplx<T> *buf, int n, int G, int p, int pad,
@@ -1456,8 +1459,9 @@ static FftGeom fft_geometry_nt(int nside, int mmax_bs, int batch, size_t csize, 
 // buffers, most of the LDS: one workgroup per CU).  Measured at Nside 1024,
 // B 16: forward 2.65 -> 2.50 ms, inverse 3.42 -> 2.91 ms; at one channel the
 // Bluestein rings' sub-transforms one at a time made the inverse 8% slower,
-// so smaller batches keep 512 threads there; at Nside 512 they take 256 (B 1
-// 63 / 64 -> 52 / 52 us, B 3 177 / 182 -> 128 / 130).
+// so smaller batches keep 512 threads there (and at Nside 2048, whose longest ring
+// needs them); at Nside 512, the one size between that and the rule above, they take
+// 256 (B 1 63 / 64 -> 52 / 52 us, B 3 177 / 182 -> 128 / 130).
 FftGeom fft_geometry(int nside, int mmax_bs, int batch, size_t csize, bool small) {
   const int Rp = 2 * nside, slots = csize == 8 ? 4096 : 2048;  // waves resident on the chip
   if (small && nside <= (batch <= 8 ? 256 : 128)) {
