@@ -97,13 +97,14 @@ __device__ __forceinline__ void mfma_split2(const u32x4 (&a0)[3], const u32x4 (&
 // have an infinite part.  So the callers hand over halves of the channels' operands
 // (spectra, coefficients), and the kernels multiply a column of them, and with it its
 // sums, by kTinyScale until the first value of kTinyBelow or more arrives.  From then
-// on values below 2^-109 lose what is under 2^-134, 2^94 times smaller than that value
-// (lambda is taken as zero below 2^-64).  The scaled operands are below 2^24 and, where
-// not zero, at least 2^-86.  In ordinary data the first operands of a wave take all its
-// columns past kTinyBelow; a wave with a column that stays below it (tiny values, a zero
+// on values below 2^-109 lose what is under 2^-134, 2^-70 of that value, where lambda
+// is taken as zero below 2^-64.  The scaled operands are below 1 and, where not zero,
+// at least 2^-86.  In ordinary data the first operands of a wave take all its columns
+// past kTinyBelow (the adjoint's coefficients, which carry the weight 4 pi / Npix, past
+// 2^-64 but not 2^-40); a wave with a column that stays below it (tiny values, a zero
 // channel) takes 3% longer (Nside 1024 L 2047 B 16, calls: analysis 2.91 -> 3.00 ms,
 // synthesis 2.68 -> 2.77).
-constexpr float kTinyBelow = 0x1p-40f;
+constexpr float kTinyBelow = 0x1p-64f;
 constexpr float kTinyScale = 0x1p64f, kTinyUndo = 0x1p-64f;
 // The scale of a lane's column (kTinyScale or 1) after the operands x(0) .. x(n - 1) of
 // this lane, and what its sums so far have to be multiplied by.  Four of the operands
