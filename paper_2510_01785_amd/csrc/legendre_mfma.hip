@@ -434,7 +434,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2,
 // exchanges 1.65.  FP32 matrix instructions in this place took 2.03 ms (Nside
 // 512 L 1535 B 12 0.67 -> 0.52 ms; Nside 256 L 767 B 64, two channel groups per
 // wave, 0.40 -> 0.30 ms).  One group of channels runs three waves per SIMD
-// (160 VGPRs; 1.88 ms with two), two groups two (242 VGPRs).
+// (167 VGPRs; 1.88 ms with two), two groups two (253 VGPRs).
 constexpr int kInvRings = 64;
 
 template <int NC>
